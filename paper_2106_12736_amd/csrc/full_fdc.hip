@@ -20,8 +20,6 @@
 // block row k of every plane lies side by side (full_spec_layout), so the planes a
 // run's contraction reads are a few MB apart rather than a plane apart.
 //
-// Complex products use four real v_mfma_f32_16x16x4f32 per 4-deep K step:
-//   re += Ar Br - Ai Bi,  im += Ar Bi + Ai Br.
 // Lane layout of v_mfma_f32_16x16x4f32 (A 16x4, B 4x16, D 16x16): lane l holds
 // A[l % 16][l / 16], B[l / 16][l % 16] and D[4 (l / 16) + j][l % 16] in register j.
 #include "device.h"
@@ -47,167 +45,301 @@ __host__ __device__ constexpr int tap_pad() {
 }
 
 // ---------------------------------------------------------------------------
-// Forward (GX = false) and dL/dX (GX = true) contraction on split-layout spectra.
+// Forward (gx = false) and dL/dX (gx = true) contraction on split-layout spectra.
 //   in  [B][KD] spectra: X (KD = Cin) or G (KD = Cout)
 //   wt  weights rearranged as [KDp][NDp][TP], zero-padded (forward: [c][s][tap];
 //       dL/dX: [s][c][tap]); KDp = KD rounded up to 4, NDp = ND rounded up to 64
 //   out [B][ND] spectra: Y (ND = Cout) or gX (ND = Cin)
-// The bins of a spectrum are cut into runs of 4: along a row of the main block
-// (same k, four consecutive l) or down the Nyquist column (four consecutive k,
-// l = P/2).  A wave owns one run, 16 batch rows and 64 outputs (four 16 x 16 D
-// tiles per bin); a workgroup is 4 waves on 4 consecutive runs and the same
-// outputs, so their weight loads coincide in L1.  Inside a run the kernel
-// spectrum factorises: for a row run K(k, l) = sum_b W^(l b) C_b with
-// C_b = sum_a w_ab W^(k a) shared by the 4 bins; for a Nyquist run W^(l b) = (-1)^b
-// and K(k, P/2) = sum_a W^(k a) R_a with R_a = sum_b (-1)^b w_ab.
-// Every load is unconditional: batch rows and channels past the end are clamped
-// to the last valid ones (their weights are zero, their outputs are not stored).
+//
+// Matrix-core tiles.  Rows m of a 16 x 16 x 4 tile are 8 images in real and imaginary
+// part, m = 2 b + part, columns 16 outputs, depth 4 channels:
+//   D += A1 Kr + A2 Ki,  A1 = (Xr; Xi),  A2 = (-Xi; Xr)   (conj K: A2 = (Xi; -Xr)),
+// so a tile holds 8 images (with a row per image, 4 images filled 4 of 16 rows and took
+// the time of 16), and a lane's four D registers are two images' complex values.
+//
+// Bins.  The weights are real, so rows k and -k of the kernel spectrum share
+// C_b = sum_a w_ab W^(k a) (conjugated for -k):
+//   K(+-k, l) = p -+ q + i (t +- r),  with v_b = W^(l b):
+//   p = sum Re v Re C, q = sum Im v Im C, r = sum Re v Im C, t = sum Im v Re C,
+// 12 operations for two bins at 3 x 3 taps (22 when each bin is formed from C alone).  A
+// workgroup (4 waves) owns the row pair (k, -k) and 4 LB columns, LB a wave; each 4-channel
+// step its threads form the C_b of 4 channels x 16 NTL outputs once, in LDS, for all waves.
+// The Nyquist column (side block, l = P/2) takes the same form with the roles of rows and
+// columns exchanged: C_a = R_a = sum_b (-1)^b w_ab is real, v_a = W^(k a), K(-k) = conj K(k).
+//
+// What bounds it: matrix and vector issue together.  On gfx950 fp32 MFMA and vector
+// instructions of one SIMD do not overlap, not even from different waves (a probe of both:
+// 6.3 ms together, 4.6 and 2.3 ms alone), so a step of 64 MFMAs (2048 cycles) and 160 vector
+// instructions (640 cycles) takes at least their sum; measured 3200-3500 cycles, i.e. 80 %.
+// Before (a row per image, bins singly): 16 images of 224^2, 64 -> 64 channels 225 -> 203 us;
+// 4 images of 512^2, 128 -> 128 channels 3.0 -> 1.68 ms; 3 images of 128^2, 48 -> 80 channels,
+// 5 x 5 taps 164 -> 64 us.  BT 8-image tiles share each K: BT = 1 with LB = 4 columns up to 8 images,
+// BT = 2 with LB = 2 beyond (the same 32 NTL accumulator registers: two waves a SIMD).
+// Every load is unconditional: images and channels past the end are clamped to the last
+// valid ones (their weights are zero, their outputs are not stored).
 // ---------------------------------------------------------------------------
-constexpr int kCtOut = 64;  // outputs per workgroup
+constexpr int kCtOut = 64;  // output padding of the rearranged weights, and the widest tile group
 
-template <int NK, bool GX, bool SIDE>
-__device__ __forceinline__ void contract_run(const float2 *__restrict__ in, const float *__restrict__ wt,
-                                             float2 *__restrict__ out, const float2 (&zs)[NK],
-                                             const float2 (&zq)[4][NK], long long pst, long long opst, int B,
-                                             int KD, int KDp, int ND, int NDp, int b0, int n0) {
-  constexpr int TP = tap_pad<NK>();
+// LDS of one step's C: [NK][4 channels][64 outputs and 16 of padding] (the padding puts the
+// channels of a wave's read on different banks), two steps' buffers.
+constexpr int kCtRow = kCtOut + 16;
+template <int NK>
+constexpr int ct_lds_elems() {
+  return 2 * NK * 4 * kCtRow;
+}
+
+// One workgroup's bins: main, row pair (k, P - k) and columns l0..l0 + LB - 1 of this wave;
+// SIDE, rows l0..l0 + LB - 1 <= P/2 and their negatives of the Nyquist column.
+template <int NK, int BT, int NTL, bool SIDE>
+__device__ __forceinline__ void contract_bins(const SpecLayout &in, const float *__restrict__ wt,
+                                              const float2 *__restrict__ tw, const SpecLayout &out, float2 *cbuf,
+                                              int B, int KD, int KDp, int ND, int NDp, int P, bool gx, int k, int l0,
+                                              int b0, int n0) {
+  constexpr int TP = tap_pad<NK>(), LB = BT == 1 ? 4 : 2;
+  const int H = P / 2;
   const int lane = threadIdx.x & 63, mrow = lane & 15, kk = lane >> 4;
-  v4f accr[4][4], acci[4][4];  // [bin q][tile t]
-#pragma unroll
-  for (int q = 0; q < 4; ++q)
-#pragma unroll
-    for (int t = 0; t < 4; ++t) accr[q][t] = acci[q][t] = v4f{0.f, 0.f, 0.f, 0.f};
+  const bool valid = SIDE ? l0 <= H : l0 < H;  // this wave's bins (idle waves run along, storing nothing)
+  if (!valid) l0 = 0;
 
-  const int ba = min(b0 + mrow, B - 1);  // A operand row (batch)
-  const float2 *arow = in + (long long)ba * KD * pst;
-  // the inputs and the weights of all four tiles are loaded one k-step ahead
-  auto load_a = [&](int k0, float4 (&a)[2]) {
-    const float4 *a4 = reinterpret_cast<const float4 *>(arow + (long long)min(k0 + kk, KD - 1) * pst);
-    a[0] = a4[0], a[1] = a4[1];
-  };
-  auto load_w = [&](int k0, int t, float4 (&w)[TP / 4]) {
-    const float4 *w4 = reinterpret_cast<const float4 *>(wt + ((long long)(k0 + kk) * NDp + n0 + 16 * t + mrow) * TP);
+  // v_b at this wave's columns (SIDE: rows)
+  float zc[LB][NK], zs[LB][NK];
 #pragma unroll
-    for (int i = 0; i < TP / 4; ++i) w[i] = w4[i];
-  };
-  float4 an[2], wn[4][TP / 4];
-  load_a(0, an);
+  for (int q = 0; q < LB; ++q) {
+    const int l = SIDE ? min(l0 + q, H) : l0 + q;
 #pragma unroll
-  for (int t = 0; t < 4; ++t) load_w(0, t, wn[t]);
-  for (int k0 = 0; k0 < KDp; k0 += 4) {
-    const float4 lo = an[0], hi = an[1];
-    float4 wc[4][TP / 4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-      for (int i = 0; i < TP / 4; ++i) wc[t][i] = wn[t][i];
-    if (k0 + 4 < KDp) {
-      load_a(k0 + 4, an);
-#pragma unroll
-      for (int t = 0; t < 4; ++t) load_w(k0 + 4, t, wn[t]);
+    for (int b = 1; b < NK; ++b) {
+      const float2 z = tw[(l * b) % P];
+      zc[q][b] = z.x, zs[q][b] = z.y;
     }
-    const float ar[4] = {lo.x, lo.z, hi.x, hi.z}, ai[4] = {lo.y, lo.w, hi.y, hi.w};
+  }
+  float2 u[NK];  // W^(k a), main
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      float w[TP];
+  for (int a = 1; a < NK; ++a) u[a] = SIDE ? make_float2(0.f, 0.f) : tw[(k * a) % P];
+
+  // this thread's element of C: channel ck, output cn
+  const int ck = threadIdx.x / (16 * NTL), cn = threadIdx.x % (16 * NTL);
+  const bool cthread = ck < 4;
+  float4 wn[TP / 4];
+  auto load_w = [&](int k0) {
+    const float4 *w4 = reinterpret_cast<const float4 *>(wt + ((long long)(k0 + (cthread ? ck : 0)) * NDp + n0 + cn) * TP);
 #pragma unroll
-      for (int i = 0; i < TP / 4; ++i)
-        w[4 * i] = wc[t][i].x, w[4 * i + 1] = wc[t][i].y, w[4 * i + 2] = wc[t][i].z, w[4 * i + 3] = wc[t][i].w;
-      // the run-invariant half of the kernel spectrum
-      float2 y[NK];
+    for (int i = 0; i < TP / 4; ++i) wn[i] = w4[i];
+  };
+  auto form_c = [&](int buf) {
+    float w[TP];
+#pragma unroll
+    for (int i = 0; i < TP / 4; ++i)
+      w[4 * i] = wn[i].x, w[4 * i + 1] = wn[i].y, w[4 * i + 2] = wn[i].z, w[4 * i + 3] = wn[i].w;
+    if (!cthread) return;
+    float2 *d = cbuf + buf * NK * 4 * kCtRow + ck * kCtRow + cn;
+    if constexpr (!SIDE) {
+#pragma unroll
+      for (int b = 0; b < NK; ++b) {  // C_b = w_0b + sum_{a>=1} w_ab u_a
+        float cx = w[b], cy = 0.f;
+#pragma unroll
+        for (int a = 1; a < NK; ++a) {
+          cx = fmaf(w[a * NK + b], u[a].x, cx);
+          cy = fmaf(w[a * NK + b], u[a].y, cy);
+        }
+        d[b * 4 * kCtRow] = make_float2(cx, cy);
+      }
+    } else {
+#pragma unroll
+      for (int a = 0; a < NK; ++a) {  // R_a = sum_b (-1)^b w_ab
+        float r = w[a * NK];
+#pragma unroll
+        for (int b = 1; b < NK; ++b) r += (b & 1) ? -w[a * NK + b] : w[a * NK + b];
+        d[a * 4 * kCtRow] = make_float2(r, 0.f);
+      }
+    }
+  };
+
+  // the inputs of this lane: image b0 + 8 i + mrow / 2 of tile i, channel k0 + kk, both rows
+  const float2 *xr[BT];
+#pragma unroll
+  for (int i = 0; i < BT; ++i) {
+    const long long plane = (long long)min(b0 + 8 * i + (mrow >> 1), B - 1) * KD;
+    xr[i] = SIDE ? in.side + plane * in.sps : in.main + plane * in.ps + l0;
+  }
+  const long long chs = SIDE ? in.sps : in.ps;
+  const long long row0 = SIDE ? 0 : k * in.rs, row1 = SIDE ? 0 : (k == 0 ? 0 : P - k) * in.rs;
+  float2 xn[BT][2][LB];
+  auto load_x = [&](int k0) {
+    const long long co = (long long)min(k0 + kk, KD - 1) * chs;
+#pragma unroll
+    for (int i = 0; i < BT; ++i) {
       if constexpr (!SIDE) {
 #pragma unroll
-        for (int b = 0; b < NK; ++b) {  // C_b = w_0b + sum_{a>=1} w_ab u_a
-          float cx = w[b], cy = 0.f;
+        for (int s = 0; s < 2; ++s) {
+          const float4 *a4 = reinterpret_cast<const float4 *>(xr[i] + co + (s ? row1 : row0));
 #pragma unroll
-          for (int a = 1; a < NK; ++a) {
-            cx = fmaf(w[a * NK + b], zs[a].x, cx);
-            cy = fmaf(w[a * NK + b], zs[a].y, cy);
+          for (int q = 0; q < LB; q += 2) {
+            const float4 a = a4[q / 2];
+            xn[i][s][q] = make_float2(a.x, a.y), xn[i][s][q + 1] = make_float2(a.z, a.w);
           }
-          y[b] = make_float2(cx, cy);
         }
       } else {
 #pragma unroll
-        for (int a = 0; a < NK; ++a) {  // R_a = sum_b (-1)^b w_ab
-          float r = w[a * NK];
+        for (int q = 0; q < LB; ++q) {
+          const int r = min(l0 + q, H);
+          xn[i][0][q] = xr[i][co + r];
+          xn[i][1][q] = xr[i][co + (r == 0 ? 0 : P - r)];
+        }
+      }
+    }
+  };
+
+  v4f acc[BT][2][LB][NTL];
 #pragma unroll
-          for (int b = 1; b < NK; ++b) r += (b & 1) ? -w[a * NK + b] : w[a * NK + b];
-          y[a] = make_float2(r, 0.f);
+  for (int i = 0; i < BT; ++i)
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int q = 0; q < LB; ++q)
+#pragma unroll
+        for (int t = 0; t < NTL; ++t) acc[i][s][q][t] = v4f{0.f, 0.f, 0.f, 0.f};
+
+  const bool im = mrow & 1;
+  const unsigned flip = (im == gx) ? 0x80000000u : 0u;  // sign of A2: -Xi on real rows, conj K the other way round
+  load_w(0);
+  load_x(0);
+  form_c(0);
+  load_w(min(4, KDp - 4));
+  __syncthreads();
+  for (int k0 = 0; k0 < KDp; k0 += 4) {
+    const int buf = (k0 >> 2) & 1;
+    float a1[BT][2][LB], a2[BT][2][LB];
+#pragma unroll
+    for (int i = 0; i < BT; ++i)
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int q = 0; q < LB; ++q) {
+          const float2 v = xn[i][s][q];
+          a1[i][s][q] = im ? v.y : v.x;
+          a2[i][s][q] = __uint_as_float(__float_as_uint(im ? v.x : v.y) ^ flip);
+          // formed here, so that the next loads can take the registers of xn: otherwise they
+          // are sunk past those loads, which then go to other registers and are copied back
+          // within this step, behind a wait for the loads just issued
+          asm volatile("" : "+v"(a1[i][s][q]), "+v"(a2[i][s][q]));
+        }
+    __builtin_amdgcn_sched_barrier(0);
+    // the next step's C (its weights arrived during the last step), inputs and weights; past
+    // the last step the last one's again, unused
+    load_x(min(k0 + 4, KDp - 4));
+    form_c(buf ^ 1);
+    load_w(min(k0 + 8, KDp - 4));
+    const float2 *cb = cbuf + buf * NK * 4 * kCtRow + kk * kCtRow + mrow;
+#pragma unroll
+    for (int t = 0; t < NTL; ++t) {
+      float2 c[NK];
+#pragma unroll
+      for (int b = 0; b < NK; ++b) c[b] = cb[b * 4 * kCtRow + 16 * t];
+      float kr[2][LB], ki[2][LB];
+#pragma unroll
+      for (int q = 0; q < LB; ++q) {
+        float p = c[0].x, tt = 0.f;
+#pragma unroll
+        for (int b = 1; b < NK; ++b) {
+          p = fmaf(zc[q][b], c[b].x, p);
+          tt = b == 1 ? zs[q][b] * c[b].x : fmaf(zs[q][b], c[b].x, tt);
+        }
+        if constexpr (!SIDE) {
+          float r = c[0].y, qq = 0.f;
+#pragma unroll
+          for (int b = 1; b < NK; ++b) {
+            r = fmaf(zc[q][b], c[b].y, r);
+            qq = b == 1 ? zs[q][b] * c[b].y : fmaf(zs[q][b], c[b].y, qq);
+          }
+          kr[0][q] = p - qq, kr[1][q] = p + qq;
+          ki[0][q] = tt + r, ki[1][q] = tt - r;
+        } else {
+          kr[0][q] = kr[1][q] = p;
+          ki[0][q] = tt, ki[1][q] = -tt;
         }
       }
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        // K = y_0 + sum_{i>=1} z_qi y_i  (z_q0 = 1)
-        float kr = y[0].x, ki = y[0].y;
+      for (int s = 0; s < 2; ++s)
 #pragma unroll
-        for (int i = 1; i < NK; ++i) {
-          if constexpr (!SIDE) {
-            kr = fmaf(zq[q][i].x, y[i].x, kr);
-            kr = fmaf(-zq[q][i].y, y[i].y, kr);
-            ki = fmaf(zq[q][i].x, y[i].y, ki);
-            ki = fmaf(zq[q][i].y, y[i].x, ki);
-          } else {
-            kr = fmaf(zq[q][i].x, y[i].x, kr);
-            ki = fmaf(zq[q][i].y, y[i].x, ki);
+        for (int q = 0; q < LB; ++q)
+#pragma unroll
+          for (int i = 0; i < BT; ++i) acc[i][s][q][t] = mfma4(a1[i][s][q], kr[s][q], acc[i][s][q][t]);
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int q = 0; q < LB; ++q)
+#pragma unroll
+          for (int i = 0; i < BT; ++i) acc[i][s][q][t] = mfma4(a2[i][s][q], ki[s][q], acc[i][s][q][t]);
+    }
+    __syncthreads();
+  }
+  if (!valid) return;
+  // D rows 4 (lane / 16) + j: images 2 (lane / 16) (registers 0, 1) and the next (2, 3)
+#pragma unroll
+  for (int i = 0; i < BT; ++i)
+#pragma unroll
+    for (int t = 0; t < NTL; ++t) {
+      const int n = n0 + 16 * t + mrow;
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int b = b0 + 8 * i + 2 * kk + j;
+        if (b >= B || n >= ND) continue;
+        const long long plane = (long long)b * ND + n;
+        if constexpr (!SIDE) {
+#pragma unroll
+          for (int s = 0; s < 2; ++s) {
+            if (s == 1 && (k == 0 || k == H)) continue;  // the pair is one row
+            float4 *o = reinterpret_cast<float4 *>(out.main + plane * out.ps + (s ? P - k : k) * out.rs + l0);
+#pragma unroll
+            for (int q = 0; q < LB; q += 2)
+              o[q / 2] = make_float4(acc[i][s][q][t][2 * j], acc[i][s][q][t][2 * j + 1], acc[i][s][q + 1][t][2 * j],
+                                     acc[i][s][q + 1][t][2 * j + 1]);
+          }
+        } else {
+          float2 *o = out.side + plane * out.sps;
+#pragma unroll
+          for (int q = 0; q < LB; ++q) {
+            const int r = l0 + q;
+            if (r > H) continue;
+            o[r] = make_float2(acc[i][0][q][t][2 * j], acc[i][0][q][t][2 * j + 1]);
+            if (r != 0 && r != H)
+              o[P - r] = make_float2(acc[i][1][q][t][2 * j], acc[i][1][q][t][2 * j + 1]);
           }
         }
-        // forward: re += Ar Kr - Ai Ki, im += Ar Ki + Ai Kr
-        // dL/dX (conj K): re += Ar Kr + Ai Ki, im += Ai Kr - Ar Ki
-        accr[q][t] = mfma4(ar[q], kr, accr[q][t]);
-        accr[q][t] = mfma4(GX ? ai[q] : -ai[q], ki, accr[q][t]);
-        acci[q][t] = mfma4(GX ? -ar[q] : ar[q], ki, acci[q][t]);
-        acci[q][t] = mfma4(ai[q], kr, acci[q][t]);
       }
     }
-  }
-  // D[m][n]: lane holds rows 4 (lane / 16) + j, column lane % 16 of each tile
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    const int n = n0 + 16 * t + mrow;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int b = b0 + 4 * kk + j;
-      if (b >= B || n >= ND) continue;
-      float4 *o = reinterpret_cast<float4 *>(out + ((long long)b * ND + n) * opst);
-      o[0] = make_float4(accr[0][t][j], acci[0][t][j], accr[1][t][j], acci[1][t][j]);
-      o[1] = make_float4(accr[2][t][j], acci[2][t][j], accr[3][t][j], acci[3][t][j]);
-    }
-  }
 }
 
-template <int NK, bool GX>
-__global__ __launch_bounds__(256) void k_full_contract(SpecLayout in, const float *__restrict__ wt,
-                                                       const float2 *__restrict__ tw, SpecLayout out, int B, int KD,
-                                                       int KDp, int ND, int NDp, int P, int nwg_run, int nsb) {
+// Workgroups per (output group, image tile): row pairs k = 0..P/2 times groups of 4 LB
+// columns, then the Nyquist column's groups of 4 LB rows 0..P/2.
+template <int BT>
+__host__ __device__ constexpr int ct_cols() {
+  return 4 * (BT == 1 ? 4 : 2);
+}
+static inline int ct_groups(int P, int cols) {
   const int H = P / 2;
-  const int nmain = P * H / 4, nrun = nmain + P / 4;
+  return (H + 1) * ((H + cols - 1) / cols) + (H + cols) / cols;
+}
+
+template <int NK, int BT, int NTL>
+__global__ __launch_bounds__(256, 2) void k_full_contract(SpecLayout in, const float *__restrict__ wt,
+                                                          const float2 *__restrict__ tw, SpecLayout out, int B, int KD,
+                                                          int KDp, int ND, int NDp, int P, int gx, int ngroups,
+                                                          int nsb, int b_first) {
+  __shared__ float2 cbuf[ct_lds_elems<NK>()];
+  constexpr int COLS = ct_cols<BT>();
+  const int H = P / 2, ncg = (H + COLS - 1) / COLS;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int blk = xcd_remap(blockIdx.x, gridDim.x);
   const int sb = blk % nsb, rest = blk / nsb;
-  const int g = (rest % nwg_run) * 4 + wave, bt = rest / nwg_run;
-  if (g >= nrun) return;  // no barriers in this kernel
-  if (g < nmain) {
-    const int k = (4 * g) / H, l0 = 4 * g - k * H;
-    float2 u[NK], v[4][NK];
-#pragma unroll
-    for (int a = 0; a < NK; ++a) u[a] = tw[(k * a) % P];
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-      for (int b = 0; b < NK; ++b) v[q][b] = tw[((l0 + q) * b) % P];
-    contract_run<NK, GX, false>(in.main + k * in.rs + l0, wt, out.main + k * out.rs + l0, u, v, in.ps, out.ps, B, KD,
-                                KDp, ND, NDp, bt * 16, sb * kCtOut);
+  const int g = rest % ngroups, b0 = b_first + (rest / ngroups) * 8 * BT, n0 = sb * 16 * NTL;
+  if (g < (H + 1) * ncg) {
+    const int k = g / ncg;
+    contract_bins<NK, BT, NTL, false>(in, wt, tw, out, cbuf, B, KD, KDp, ND, NDp, P, gx != 0, k,
+                                      (g - k * ncg) * COLS + wave * (COLS / 4), b0, n0);
   } else {
-    const int k0 = 4 * (g - nmain);
-    float2 z[NK], u[4][NK];
-#pragma unroll
-    for (int b = 0; b < NK; ++b) z[b] = make_float2((b & 1) ? -1.f : 1.f, 0.f);
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-      for (int a = 0; a < NK; ++a) u[q][a] = tw[((k0 + q) * a) % P];
-    contract_run<NK, GX, true>(in.side + k0, wt, out.side + k0, z, u, in.sps, out.sps, B, KD, KDp, ND, NDp, bt * 16,
-                               sb * kCtOut);
+    contract_bins<NK, BT, NTL, true>(in, wt, tw, out, cbuf, B, KD, KDp, ND, NDp, P, gx != 0, 0,
+                                     (g - (H + 1) * ncg) * COLS + wave * (COLS / 4), b0, n0);
   }
 }
 
@@ -583,21 +715,46 @@ hipError_t launch_full_weights(const float *w, float *wt, bool gx, int S, int C,
 
 hipError_t launch_full_contract(bool gx, int nk, SpecLayout in, const float *wt, const float2 *tw, SpecLayout out,
                                 int B, int KD, int ND, int P, hipStream_t s) {
-  const int nrun = P * (P / 2) / 4 + P / 4;
-  const int nwg_run = (nrun + 3) / 4, nsb = (ND + kCtOut - 1) / kCtOut, nbt = (B + 15) / 16;
-  const long long blocks = (long long)nwg_run * nsb * nbt;
-  if (blocks >= (1LL << 31) || P % 8 != 0) return hipErrorInvalidValue;
+  if (P % 8 != 0) return hipErrorInvalidValue;
   const int KDp = round_up(KD, 4), NDp = round_up(ND, kCtOut);
+  // output groups of NTL 16-output tiles: as few groups as 64 outputs give, each as narrow
+  // as they allow (80 outputs: two groups of 48 instead of two of 64)
+  const int tiles = (ND + 15) / 16, nsb = (tiles + 3) / 4;
+  const char *nm = gx ? "full_contract_gx" : "full_contract_fwd";
   hipError_t err = hipErrorInvalidValue;
+  // 16-image tiles, and 8-image tiles for the last 8 or fewer images
+  const int n16 = (B + 7) / 8 / 2, rest = B - 16 * n16;
   dispatch_nk(nk, [&](auto nc) {
     constexpr int NK = decltype(nc)::value;
-    const char *nm = gx ? "full_contract_gx" : "full_contract_fwd";
-    if (gx)
-      err = timed_launch(nm, k_full_contract<NK, true>, dim3((unsigned)blocks), dim3(256), 0, s, in, wt, tw, out, B,
-                         KD, KDp, ND, NDp, P, nwg_run, nsb);
-    else
-      err = timed_launch(nm, k_full_contract<NK, false>, dim3((unsigned)blocks), dim3(256), 0, s, in, wt, tw, out, B,
-                         KD, KDp, ND, NDp, P, nwg_run, nsb);
+    auto go = [&](auto btc, auto ntc, int b_first, long long nbt) {
+      constexpr int BT = decltype(btc)::value, NTL = decltype(ntc)::value;
+      const int ng = ct_groups(P, ct_cols<BT>());
+      const long long per = (long long)ng * nsb, most = ((1LL << 31) - 1) / per;  // image tiles a launch can take
+      if (most < 1) {
+        err = hipErrorInvalidValue;
+        return;
+      }
+      for (long long i = 0; i < nbt; i += most) {
+        const long long n = std::min(most, nbt - i);
+        err = timed_launch(nm, k_full_contract<NK, BT, NTL>, dim3((unsigned)(per * n)), dim3(256), 0, s, in, wt, tw,
+                           out, B, KD, KDp, ND, NDp, P, gx ? 1 : 0, ng, nsb, (int)(b_first + i * 8 * BT));
+        if (err != hipSuccess) return;
+      }
+    };
+    auto with_ntl = [&](auto ntc) {
+      if (n16 > 0) go(std::integral_constant<int, 2>{}, ntc, 0, n16);
+      if (n16 > 0 && err != hipSuccess) return;
+      if (rest > 0) go(std::integral_constant<int, 1>{}, ntc, 16 * n16, 1);
+    };
+    if constexpr (NK == 3 || NK == 5) {
+      switch ((tiles + nsb - 1) / nsb) {
+        case 1: with_ntl(std::integral_constant<int, 1>{}); return;
+        case 2: with_ntl(std::integral_constant<int, 2>{}); return;
+        case 3: with_ntl(std::integral_constant<int, 3>{}); return;
+        default: break;
+      }
+    }
+    with_ntl(std::integral_constant<int, 4>{});
   });
   return err;
 }

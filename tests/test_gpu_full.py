@@ -80,6 +80,49 @@ def test_full_layer_forward_backward(B, Cin, Cout, P, n, artifact):
     assert_parity(to_np(gw), gw_ref, "gw")
 
 
+# Edges of the contraction's tiles: image groups of 8 and 16 (and the rest after whole
+# groups), output groups of one to four 16-output tiles and two of them, channel steps of 4,
+# column groups wider than the spectrum (P = 8) or with a ragged last one (P = 224), each
+# kernel size.
+CONTRACT_CASES = [
+    # B, Cin, Cout, P, n
+    (1, 4, 16, 8, 3),
+    (8, 16, 17, 16, 3),
+    (9, 17, 33, 16, 3),
+    (16, 33, 49, 32, 3),
+    (20, 49, 65, 8, 5),
+    (24, 3, 80, 16, 5),
+    (25, 80, 5, 16, 1),
+    (4, 33, 20, 224, 3),
+    (7, 65, 18, 32, 2),
+    (12, 20, 35, 64, 4),
+    (6, 130, 20, 64, 5),
+]
+
+
+@pytest.mark.parametrize("B,Cin,Cout,P,n", CONTRACT_CASES)
+def test_full_contraction_tiles(B, Cin, Cout, P, n):
+    """Forward and dL/dX at the tile edges.  Four transforms of log2(P) <= 8 roundings each
+    and a sum over at most 130 channels of products, in units of u = 6e-8 and adding as a
+    random walk, stay below 20 u = 1.2e-6; the bound is four times that."""
+    print(f"full contraction B={B} Cin={Cin} Cout={Cout} P={P} n={n}", flush=True)
+    rng = _rng("full-tiles", B, Cin, Cout, P, n)
+    x = inputs.normal(rng, (B, Cin, P, P))
+    w = inputs.he_normal_weights(rng, Cout, Cin, n)
+    gy = inputs.normal(rng, (B, Cout, P, P))
+    layer = layers.FullLayer(B, Cin, Cout, P, kernel_n=n, artifact="roll")
+    saved = layer.new_saved()
+    wd = _gpu(w)
+    y = layer.forward(_gpu(x), wd, saved=saved)
+    gx, gw = layer.backward(_gpu(gy), saved, wd)
+    torch.cuda.synchronize()
+    y_ref, xs_ref = fdc.full_fdc_forward(x.astype(np.float64), w.astype(np.float64), fdc.ARTIFACT_ROLL)
+    gx_ref, gw_ref = fdc.full_fdc_backward(gy.astype(np.float64), xs_ref, w.astype(np.float64), fdc.ARTIFACT_ROLL)
+    assert_parity(to_np(y), y_ref, "y", rel=5e-6)
+    assert_parity(to_np(gx), gx_ref, "gx", rel=5e-6)
+    assert_parity(to_np(gw), gw_ref, "gw", rel=5e-6)
+
+
 def test_full_layer_optional_outputs_and_repeatability():
     """Forward without `saved`, backward with only one of the two gradients, and
     bit-identical results on a second call (fixed reduction order)."""
