@@ -29,6 +29,7 @@
 
 #include <algorithm>
 #include <string>
+#include <type_traits>
 
 namespace fdc {
 
@@ -36,6 +37,14 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ v4f mfma4(float a, float b, v4f c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+template <class F>
+__device__ __forceinline__ void static_for4(F &&f) {
+  f(std::integral_constant<int, 0>{});
+  f(std::integral_constant<int, 1>{});
+  f(std::integral_constant<int, 2>{});
+  f(std::integral_constant<int, 3>{});
 }
 
 // Taps of an n x n kernel, padded to a multiple of 4 for whole 16-byte loads.
@@ -88,50 +97,39 @@ constexpr int ct_lds_elems() {
   return 2 * NK * 4 * kCtRow;
 }
 
-// One workgroup's bins: main, row pair (k, P - k) and columns l0..l0 + LB - 1 of this wave;
-// SIDE, rows l0..l0 + LB - 1 <= P/2 and their negatives of the Nyquist column.
-template <int NK, int BT, int NTL, bool SIDE>
-__device__ __forceinline__ void contract_bins(const SpecLayout &in, const float *__restrict__ wt,
-                                              const float2 *__restrict__ tw, const SpecLayout &out, float2 *cbuf,
-                                              int B, int KD, int KDp, int ND, int NDp, int P, bool gx, int k, int l0,
-                                              int b0, int n0) {
-  constexpr int TP = tap_pad<NK>(), LB = BT == 1 ? 4 : 2;
-  const int H = P / 2;
-  const int lane = threadIdx.x & 63, mrow = lane & 15, kk = lane >> 4;
-  const bool valid = SIDE ? l0 <= H : l0 < H;  // this wave's bins (idle waves run along, storing nothing)
-  if (!valid) l0 = 0;
-
-  // v_b at this wave's columns (SIDE: rows)
-  float zc[LB][NK], zs[LB][NK];
-#pragma unroll
-  for (int q = 0; q < LB; ++q) {
-    const int l = SIDE ? min(l0 + q, H) : l0 + q;
-#pragma unroll
-    for (int b = 1; b < NK; ++b) {
-      const float2 z = tw[(l * b) % P];
-      zc[q][b] = z.x, zs[q][b] = z.y;
-    }
-  }
-  float2 u[NK];  // W^(k a), main
-#pragma unroll
-  for (int a = 1; a < NK; ++a) u[a] = SIDE ? make_float2(0.f, 0.f) : tw[(k * a) % P];
-
-  // this thread's element of C: channel ck, output cn
-  const int ck = threadIdx.x / (16 * NTL), cn = threadIdx.x % (16 * NTL);
-  const bool cthread = ck < 4;
+// The workgroup's C_b of 4 channels x 16 NTL outputs (from n0): each thread loads the weights
+// of one (channel, output) and forms its C_b (SIDE: R_a) into one of the two step buffers.
+template <int NK, int NTL, bool SIDE>
+struct KernelRows {
+  static constexpr int TP = tap_pad<NK>();
+  const float *w0;
+  long long kstride;
+  float2 *dst;
+  float2 u[NK];  // W^(k a)
   float4 wn[TP / 4];
-  auto load_w = [&](int k0) {
-    const float4 *w4 = reinterpret_cast<const float4 *>(wt + ((long long)(k0 + (cthread ? ck : 0)) * NDp + n0 + cn) * TP);
+  bool mine;
+  __device__ __forceinline__ KernelRows(const float *wt, const float2 *tw, float2 *cbuf, int NDp, int n0, int P,
+                                        int k) {
+    const int ck = threadIdx.x / (16 * NTL), cn = threadIdx.x % (16 * NTL);
+    mine = ck < 4;
+    w0 = wt + ((long long)(mine ? ck : 0) * NDp + n0 + cn) * TP;
+    kstride = (long long)NDp * TP;
+    dst = cbuf + (mine ? ck : 0) * kCtRow + cn;
+#pragma unroll
+    for (int a = 1; a < NK; ++a) u[a] = SIDE ? make_float2(0.f, 0.f) : tw[(k * a) % P];
+  }
+  __device__ __forceinline__ void load(int k0) {
+    const float4 *w4 = reinterpret_cast<const float4 *>(w0 + k0 * kstride);
 #pragma unroll
     for (int i = 0; i < TP / 4; ++i) wn[i] = w4[i];
-  };
-  auto form_c = [&](int buf) {
+  }
+  __device__ __forceinline__ void form(int buf) const {
     float w[TP];
 #pragma unroll
     for (int i = 0; i < TP / 4; ++i)
       w[4 * i] = wn[i].x, w[4 * i + 1] = wn[i].y, w[4 * i + 2] = wn[i].z, w[4 * i + 3] = wn[i].w;
-    if (!cthread) return;
-    float2 *d = cbuf + buf * NK * 4 * kCtRow + ck * kCtRow + cn;
+    if (!mine) return;
+    float2 *d = dst + buf * NK * 4 * kCtRow;
     if constexpr (!SIDE) {
 #pragma unroll
       for (int b = 0; b < NK; ++b) {  // C_b = w_0b + sum_{a>=1} w_ab u_a
@@ -152,7 +150,60 @@ __device__ __forceinline__ void contract_bins(const SpecLayout &in, const float 
         d[a * 4 * kCtRow] = make_float2(r, 0.f);
       }
     }
-  };
+  }
+};
+
+// Kernel spectrum at rows +-k (SIDE: rows +-r) of one column (row) from its C (R) and phases
+// v_b = zc + i zs: kr, ki[0] for +, [1] for -.
+template <int NK, bool SIDE>
+__device__ __forceinline__ void kernel_pair(const float2 (&c)[NK], const float (&zc)[NK], const float (&zs)[NK],
+                                            float (&kr)[2], float (&ki)[2]) {
+  float p = c[0].x, t = 0.f;
+#pragma unroll
+  for (int b = 1; b < NK; ++b) {
+    p = fmaf(zc[b], c[b].x, p);
+    t = b == 1 ? zs[b] * c[b].x : fmaf(zs[b], c[b].x, t);
+  }
+  if constexpr (!SIDE) {
+    float r = c[0].y, q = 0.f;
+#pragma unroll
+    for (int b = 1; b < NK; ++b) {
+      r = fmaf(zc[b], c[b].y, r);
+      q = b == 1 ? zs[b] * c[b].y : fmaf(zs[b], c[b].y, q);
+    }
+    kr[0] = p - q, kr[1] = p + q;
+    ki[0] = t + r, ki[1] = t - r;
+  } else {
+    kr[0] = kr[1] = p;
+    ki[0] = t, ki[1] = -t;
+  }
+}
+
+// One workgroup's bins: main, row pair (k, P - k) and columns l0..l0 + LB - 1 of this wave;
+// SIDE, rows l0..l0 + LB - 1 <= P/2 and their negatives of the Nyquist column.
+template <int NK, int BT, int NTL, bool SIDE>
+__device__ __forceinline__ void contract_bins(const SpecLayout &in, const float *__restrict__ wt,
+                                              const float2 *__restrict__ tw, const SpecLayout &out, float2 *cbuf,
+                                              int B, int KD, int KDp, int ND, int NDp, int P, bool gx, int k, int l0,
+                                              int b0, int n0) {
+  constexpr int LB = BT == 1 ? 4 : 2;
+  const int H = P / 2;
+  const int lane = threadIdx.x & 63, mrow = lane & 15, kk = lane >> 4;
+  const bool valid = SIDE ? l0 <= H : l0 < H;  // this wave's bins (idle waves run along, storing nothing)
+  if (!valid) l0 = 0;
+
+  // v_b at this wave's columns (SIDE: rows)
+  float zc[LB][NK], zs[LB][NK];
+#pragma unroll
+  for (int q = 0; q < LB; ++q) {
+    const int l = SIDE ? min(l0 + q, H) : l0 + q;
+#pragma unroll
+    for (int b = 1; b < NK; ++b) {
+      const float2 z = tw[(l * b) % P];
+      zc[q][b] = z.x, zs[q][b] = z.y;
+    }
+  }
+  KernelRows<NK, NTL, SIDE> rows(wt, tw, cbuf, NDp, n0, P, k);
 
   // the inputs of this lane: image b0 + 8 i + mrow / 2 of tile i, channel k0 + kk, both rows
   const float2 *xr[BT];
@@ -201,10 +252,10 @@ __device__ __forceinline__ void contract_bins(const SpecLayout &in, const float 
 
   const bool im = mrow & 1;
   const unsigned flip = (im == gx) ? 0x80000000u : 0u;  // sign of A2: -Xi on real rows, conj K the other way round
-  load_w(0);
+  rows.load(0);
   load_x(0);
-  form_c(0);
-  load_w(min(4, KDp - 4));
+  rows.form(0);
+  rows.load(min(4, KDp - 4));
   __syncthreads();
   for (int k0 = 0; k0 < KDp; k0 += 4) {
     const int buf = (k0 >> 2) & 1;
@@ -227,8 +278,8 @@ __device__ __forceinline__ void contract_bins(const SpecLayout &in, const float 
     // the next step's C (its weights arrived during the last step), inputs and weights; past
     // the last step the last one's again, unused
     load_x(min(k0 + 4, KDp - 4));
-    form_c(buf ^ 1);
-    load_w(min(k0 + 8, KDp - 4));
+    rows.form(buf ^ 1);
+    rows.load(min(k0 + 8, KDp - 4));
     const float2 *cb = cbuf + buf * NK * 4 * kCtRow + kk * kCtRow + mrow;
 #pragma unroll
     for (int t = 0; t < NTL; ++t) {
@@ -238,25 +289,9 @@ __device__ __forceinline__ void contract_bins(const SpecLayout &in, const float 
       float kr[2][LB], ki[2][LB];
 #pragma unroll
       for (int q = 0; q < LB; ++q) {
-        float p = c[0].x, tt = 0.f;
-#pragma unroll
-        for (int b = 1; b < NK; ++b) {
-          p = fmaf(zc[q][b], c[b].x, p);
-          tt = b == 1 ? zs[q][b] * c[b].x : fmaf(zs[q][b], c[b].x, tt);
-        }
-        if constexpr (!SIDE) {
-          float r = c[0].y, qq = 0.f;
-#pragma unroll
-          for (int b = 1; b < NK; ++b) {
-            r = fmaf(zc[q][b], c[b].y, r);
-            qq = b == 1 ? zs[q][b] * c[b].y : fmaf(zs[q][b], c[b].y, qq);
-          }
-          kr[0][q] = p - qq, kr[1][q] = p + qq;
-          ki[0][q] = tt + r, ki[1][q] = tt - r;
-        } else {
-          kr[0][q] = kr[1][q] = p;
-          ki[0][q] = tt, ki[1][q] = -tt;
-        }
+        float r2[2], i2[2];
+        kernel_pair<NK, SIDE>(c, zc[q], zs[q], r2, i2);
+        kr[0][q] = r2[0], kr[1][q] = r2[1], ki[0][q] = i2[0], ki[1][q] = i2[1];
       }
 #pragma unroll
       for (int s = 0; s < 2; ++s)
@@ -310,6 +345,152 @@ __device__ __forceinline__ void contract_bins(const SpecLayout &in, const float 
     }
 }
 
+// The same for at most 4 images, on v_mfma_f32_4x4x1f32 (16 blocks of 4 x 4 x 1, 8 cycles, the
+// rate of the larger tiles): rows are the 4 images, a block's columns 4 outputs, so a wave
+// takes 64 outputs (lane n) and no row is idle: 32 cycles for 64 kernel bins where a half-empty
+// 16 x 16 tile takes 64.  The A operand comes from one block, broadcast to all 16 (CBSZ = 4,
+// ABID): block b of a lane's load holds channel b / 4, row +-k (b / 2 % 2) and columns
+// 2 (b % 2), 2 (b % 2) + 1 of the wave's four, one 16-byte load a 4-channel step.
+// A 4-channel step is 128 MFMAs (1024 cycles) and 192 vector instructions for K (768).
+template <int NK, bool SIDE>
+__device__ __forceinline__ void contract4_bins(const SpecLayout &in, const float *__restrict__ wt,
+                                               const float2 *__restrict__ tw, const SpecLayout &out, float2 *cbuf,
+                                               int B, int KD, int KDp, int ND, int NDp, int P, bool gx, int k, int l0,
+                                               int b0, int n0) {
+  constexpr int LB = 4;
+  const int H = P / 2;
+  const int lane = threadIdx.x & 63, blk = lane >> 2;
+  const bool valid = SIDE ? l0 <= H : l0 < H;
+  if (!valid) l0 = 0;
+
+  float zc[LB][NK], zs[LB][NK];
+#pragma unroll
+  for (int q = 0; q < LB; ++q) {
+    const int l = SIDE ? min(l0 + q, H) : l0 + q;
+#pragma unroll
+    for (int b = 1; b < NK; ++b) {
+      const float2 z = tw[(l * b) % P];
+      zc[q][b] = z.x, zs[q][b] = z.y;
+    }
+  }
+  KernelRows<NK, 4, SIDE> rows(wt, tw, cbuf, NDp, n0, P, k);
+
+  // this lane's inputs: image b0 + lane % 4, channel k0 + blk / 4, row +-k, two columns
+  const int ch = blk >> 2, xs = (blk >> 1) & 1, xh = 2 * (blk & 1);
+  const long long plane = (long long)min(b0 + (lane & 3), B - 1) * KD;
+  const float2 *xp;
+  int off1 = 0;  // SIDE: the second bin relative to the first
+  if constexpr (!SIDE) {
+    xp = in.main + plane * in.ps + (long long)(xs ? (k == 0 ? 0 : P - k) : k) * in.rs + l0 + xh;
+  } else {
+    const int r0 = min(l0 + xh, H), r1 = min(l0 + xh + 1, H);
+    const int e0 = xs ? (r0 == 0 ? 0 : P - r0) : r0, e1 = xs ? (r1 == 0 ? 0 : P - r1) : r1;
+    xp = in.side + plane * in.sps + e0;
+    off1 = e1 - e0;
+  }
+  const long long chs = SIDE ? in.sps : in.ps;
+  float4 xn;
+  auto load_x = [&](int k0) {
+    const float2 *q = xp + min(k0 + ch, KD - 1) * chs;
+    if constexpr (!SIDE) {
+      xn = *reinterpret_cast<const float4 *>(q);
+    } else {
+      const float2 u = q[0], v = q[off1];
+      xn = make_float4(u.x, u.y, v.x, v.y);
+    }
+  };
+
+  v4f ar[2][LB], ai[2][LB];
+#pragma unroll
+  for (int s = 0; s < 2; ++s)
+#pragma unroll
+    for (int q = 0; q < LB; ++q) ar[s][q] = ai[s][q] = v4f{0.f, 0.f, 0.f, 0.f};
+
+  rows.load(0);
+  load_x(0);
+  rows.form(0);
+  rows.load(min(4, KDp - 4));
+  __syncthreads();
+  for (int k0 = 0; k0 < KDp; k0 += 4) {
+    const int buf = (k0 >> 2) & 1;
+    // re += Xr Kr + pr Ki, im += Xi Kr + pi Ki:  (pr, pi) = (-Xi, Xr), conj K: (Xi, -Xr)
+    float xr[2], xi[2], pr[2], pi[2];
+    xr[0] = xn.x, xi[0] = xn.y, xr[1] = xn.z, xi[1] = xn.w;
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      pr[e] = gx ? xi[e] : -xi[e], pi[e] = gx ? -xr[e] : xr[e];
+      // (formed before the next loads, see contract_bins)
+      asm volatile("" : "+v"(xr[e]), "+v"(xi[e]), "+v"(pr[e]), "+v"(pi[e]));
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    load_x(min(k0 + 4, KDp - 4));
+    rows.form(buf ^ 1);
+    rows.load(min(k0 + 8, KDp - 4));
+    const float2 *cb = cbuf + buf * NK * 4 * kCtRow + lane;
+    static_for4([&](auto xc) {
+      constexpr int x = decltype(xc)::value;
+      float2 c[NK];
+#pragma unroll
+      for (int b = 0; b < NK; ++b) c[b] = cb[(b * 4 + x) * kCtRow];
+      float kr[2][LB], ki[2][LB];
+#pragma unroll
+      for (int q = 0; q < LB; ++q) {
+        float r2[2], i2[2];
+        kernel_pair<NK, SIDE>(c, zc[q], zs[q], r2, i2);
+        kr[0][q] = r2[0], kr[1][q] = r2[1], ki[0][q] = i2[0], ki[1][q] = i2[1];
+      }
+      auto mul = [&](auto sc, auto hc) {
+        constexpr int s = decltype(sc)::value, h = decltype(hc)::value, id = 4 * x + 2 * s + h;
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          const int q = 2 * h + e;
+          ar[s][q] = __builtin_amdgcn_mfma_f32_4x4x1f32(xr[e], kr[s][q], ar[s][q], 4, id, 0);
+          ai[s][q] = __builtin_amdgcn_mfma_f32_4x4x1f32(xi[e], kr[s][q], ai[s][q], 4, id, 0);
+        }
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          const int q = 2 * h + e;
+          ar[s][q] = __builtin_amdgcn_mfma_f32_4x4x1f32(pr[e], ki[s][q], ar[s][q], 4, id, 0);
+          ai[s][q] = __builtin_amdgcn_mfma_f32_4x4x1f32(pi[e], ki[s][q], ai[s][q], 4, id, 0);
+        }
+      };
+      using I0 = std::integral_constant<int, 0>;
+      using I1 = std::integral_constant<int, 1>;
+      mul(I0{}, I0{});
+      mul(I0{}, I1{});
+      mul(I1{}, I0{});
+      mul(I1{}, I1{});
+    });
+    __syncthreads();
+  }
+  const int n = n0 + lane;
+  if (!valid || n >= ND) return;
+  // D register r: image b0 + r of output n
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    if (b0 + r >= B) continue;
+    const long long pl = (long long)(b0 + r) * ND + n;
+    if constexpr (!SIDE) {
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        if (s == 1 && (k == 0 || k == H)) continue;  // the pair is one row
+        float4 *o = reinterpret_cast<float4 *>(out.main + pl * out.ps + (s ? P - k : k) * out.rs + l0);
+        o[0] = make_float4(ar[s][0][r], ai[s][0][r], ar[s][1][r], ai[s][1][r]);
+        o[1] = make_float4(ar[s][2][r], ai[s][2][r], ar[s][3][r], ai[s][3][r]);
+      }
+    } else {
+      float2 *o = out.side + pl * out.sps;
+#pragma unroll
+      for (int q = 0; q < LB; ++q) {
+        const int row = l0 + q;
+        if (row > H) continue;
+        o[row] = make_float2(ar[0][q][r], ai[0][q][r]);
+        if (row != 0 && row != H) o[P - row] = make_float2(ar[1][q][r], ai[1][q][r]);
+      }
+    }
+  }
+}
+
 // Workgroups per (output group, image tile): row pairs k = 0..P/2 times groups of 4 LB
 // columns, then the Nyquist column's groups of 4 LB rows 0..P/2.
 template <int BT>
@@ -340,6 +521,28 @@ __global__ __launch_bounds__(256, 2) void k_full_contract(SpecLayout in, const f
   } else {
     contract_bins<NK, BT, NTL, true>(in, wt, tw, out, cbuf, B, KD, KDp, ND, NDp, P, gx != 0, 0,
                                      (g - (H + 1) * ncg) * COLS + wave * (COLS / 4), b0, n0);
+  }
+}
+
+// 4 images, 64 outputs a workgroup (grid as k_full_contract with BT = 1, one image tile).
+template <int NK>
+__global__ __launch_bounds__(256, 3) void k_full_contract4(SpecLayout in, const float *__restrict__ wt,
+                                                           const float2 *__restrict__ tw, SpecLayout out, int B,
+                                                           int KD, int KDp, int ND, int NDp, int P, int gx, int nsb,
+                                                           int b0) {
+  __shared__ float2 cbuf[ct_lds_elems<NK>()];
+  constexpr int COLS = ct_cols<1>();
+  const int H = P / 2, ncg = (H + COLS - 1) / COLS;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int blk = xcd_remap(blockIdx.x, gridDim.x);
+  const int g = blk / nsb, n0 = (blk - g * nsb) * kCtOut;
+  if (g < (H + 1) * ncg) {
+    const int k = g / ncg;
+    contract4_bins<NK, false>(in, wt, tw, out, cbuf, B, KD, KDp, ND, NDp, P, gx != 0, k,
+                              (g - k * ncg) * COLS + wave * 4, b0, n0);
+  } else {
+    contract4_bins<NK, true>(in, wt, tw, out, cbuf, B, KD, KDp, ND, NDp, P, gx != 0, 0,
+                             (g - (H + 1) * ncg) * COLS + wave * 4, b0, n0);
   }
 }
 
@@ -746,6 +949,27 @@ hipError_t launch_full_contract(bool gx, int nk, SpecLayout in, const float *wt,
       if (n16 > 0 && err != hipSuccess) return;
       if (rest > 0) go(std::integral_constant<int, 1>{}, ntc, 16 * n16, 1);
     };
+    // the last 1 to 4 images: 64 outputs a workgroup without idle rows, about 62 cycles for 64
+    // kernel bins (3 x 3) where 8-image tiles take about 98, unless 16-output tiles waste less:
+    // up to 32 of 64 outputs at 3 x 3 taps, up to 48 at 5 x 5, where K takes more of both (48
+    // outputs of 128^2, 3 images: 68 us here, 65 on 8-image tiles; 128 -> 128 channels of
+    // 512^2, 4 images, 3 x 3: 1.12 ms here, 1.68 there)
+    if constexpr (NK == 3 || NK == 5) {
+      if (rest > 0 && rest <= 4 && (NK == 3 ? 2 * tiles >= 5 * nsb : 5 * tiles >= 16 * nsb)) {
+        if (n16 > 0) {
+          err = launch_full_contract(gx, nk, in, wt, tw, out, 16 * n16, KD, ND, P, s);
+          if (err != hipSuccess) return;
+        }
+        const long long grid = (long long)ct_groups(P, ct_cols<1>()) * nsb;
+        if (grid >= (1LL << 31)) {
+          err = hipErrorInvalidValue;
+          return;
+        }
+        err = timed_launch(nm, k_full_contract4<NK>, dim3((unsigned)grid), dim3(256), 0, s, in, wt, tw, out, B, KD,
+                           KDp, ND, NDp, P, gx ? 1 : 0, nsb, 16 * n16);
+        return;
+      }
+    }
     if constexpr (NK == 3 || NK == 5) {
       switch ((tiles + nsb - 1) / nsb) {
         case 1: with_ntl(std::integral_constant<int, 1>{}); return;

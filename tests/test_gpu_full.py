@@ -97,6 +97,8 @@ CONTRACT_CASES = [
     (7, 65, 18, 32, 2),
     (12, 20, 35, 64, 4),
     (6, 130, 20, 64, 5),
+    (1, 35, 70, 32, 3),    # 4-image tiles: 64-output groups, the second ragged; channels past 4
+    (19, 41, 64, 16, 5),   # ... after 16-image tiles
 ]
 
 
