@@ -1005,7 +1005,7 @@ FullWs full_layout(int B, int Cin, int Cout, int P, int kn, size_t *fwd, size_t 
   w.gx = align256(w.g + ys);
   w.wg = align256(w.gx + xs);
   w.part = align256(w.wg + fdc::full_weight_floats(Cout, Cin, kn) * sizeof(float));
-  *bwd = align256(w.part + (size_t)fdc::full_gw_chunks(B, Cout, Cin, P, kn) * Cout * Cin * kn * kn * sizeof(float));
+  *bwd = align256(w.part + fdc::full_gw_part_floats(B, Cout, Cin, P, kn) * sizeof(float));
   return w;
 }
 }  // namespace

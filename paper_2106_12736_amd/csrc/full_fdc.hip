@@ -547,306 +547,319 @@ __global__ __launch_bounds__(256, 3) void k_full_contract4(SpecLayout in, const 
 }
 
 // ---------------------------------------------------------------------------
-// dL/dw partial sums over one chunk of runs (runs as in the contraction).
-//   G [B][S], X [B][C] split-layout spectra; part [chunk][S][C][NK*NK] float
-// Per bin gK[s][c] = sum_b G[b][s] conj(X[b][c]) on the matrix cores (M = s, N = c,
-// K-dim = b, 4 batch rows per step), then
-//   dL/dw[s][c][a][b] = Re sum_bins gK conj(W^(k a) W^(l b)),
-// done per run: a row run sums E_b = sum_q gK_q conj(W^(l_q b)) and adds
-// Re(E_b conj(W^(k a))); a Nyquist run sums F_a = sum_q gK_q conj(W^(k_q a)) and adds
-// (-1)^b Re(F_a).  A workgroup (4 waves) owns a 32 x 32 (s, c) block, each wave a
-// 16 x 16 tile, and walks its chunk one run (4 bins) at a time, 4 batch rows per step.
-// A step's G and X rows are loaded once per workgroup and staged in LDS, and the
-// loads of step t + 2 are in flight while step t computes.  Loads are unconditional:
-// batch rows past the end are clamped and staged as zeros, channels and runs past the
-// end are clamped and their results dropped.
+// dL/dw partial sums.  G [B][S], X [B][C] split-layout spectra.
+// Per bin D[s][c] = sum_b G[b][s] conj(X[b][c]) on the matrix cores (M = s, N = c, depth =
+// images, 4 a step), then the adjoint of the kernel spectrum,
+//   dL/dw[s][c][a][b] = Re sum_bins D conj(u_a(k) v_b(l)),  u_a = W^(k a), v_b = W^(l b).
+// Over a row pair (k, -k), with u_a(-k) = conj u_a(k), P = D(k) + D(-k), Q = D(k) - D(-k):
+//   sum = Re u_a EP_b + Im u_a EQ_b,  EP_b = sum_l Re(P conj v_b), EQ_b = sum_l Im(Q conj v_b),
+// so that a bin costs 2 + 2.5 NK vector instructions (13 of them before at 3 x 3 taps, now 7)
+// and the a-sum is left to the reduction, once per row pair: a workgroup keeps 2 NK sums a
+// (s, c) instead of NK^2.  The Nyquist column l = P/2 runs as one more "row" over k < P/2 with
+// rows k and k + P/2 as its pair: u_a(k + P/2) = (-1)^a u_a(k),
+//   dL/dw += (-1)^b EP_a,  EP_a = sum_k Re((D(k) + (-1)^a D(k + P/2)) conj u_a).
+//
+// A workgroup of 16 waves owns a 32 x 32 (s, c) block of one row pair (or part of its
+// columns): each wave a 16 x 16 tile and a quarter of the columns in flight.  A stage is LB
+// columns of both rows for IMG images: 32 G and 32 X planes, LB * 8 bytes each, loaded by LB/2
+// neighbouring lanes and staged in LDS; the loads of stage t + 2 are in flight and stage t + 1
+// is written while stage t is multiplied.  IMG = 8, LB = 8 (64-byte pieces); up to 4 images
+// IMG = 4, LB = 16 (whole 128-byte lines).  What bounds it: matrix plus vector issue (they do
+// not overlap), and reading the spectra from L2, S/32 + C/32 times: with 32-byte pieces (one
+// run of 4 columns) every piece was a request of its own, 21 TB/s of lines at 256 channels.
+// Measured, pass and reduction, before and after: 16 images of 224^2, 64 x 64 channels 294 ->
+// 205 us, 256 x 256 2.66 -> 2.37 ms; 4 images of 512^2, 128 x 128 1.50 -> 1.13 ms; 3 images of
+// 128^2, 80 x 48, 5 x 5 taps 225 -> 92 us (the NK^2 sums had spilled).
 // ---------------------------------------------------------------------------
-// Twiddles W^i for i < n P in LDS: every phase index the projection forms (k a,
-// (l + q) b with k < P, l + q < P/2, a, b < n) is then a plain table index.
-template <int NK>
-__host__ __device__ constexpr int gw_tw_elems(int P) {
-  return (NK * P + 31) & ~31;
-}
+template <int IMG>
+struct GwStage {
+  static constexpr int LB = IMG == 8 ? 8 : 16;       // columns a stage
+  static constexpr int RS = 2 * LB + 2;              // complex values a plane: both rows, and 2 that spread the banks
+  static constexpr int IMAGE = 64 * RS, BUF = IMG * IMAGE;
+};
+constexpr int kGwThreads = 1024;
+// floats of a partial sum: EP_b and EQ_b (for 1 x 1 kernels EP_0 alone)
+constexpr int gw_record(int nk) { return nk == 1 ? 1 : 2 * nk; }
 
-// Adds one run's gK (4 bins: dr/di[q], lane rows j) projected onto the taps to gw.
-// Row run (k, l0..l0+3); Nyquist run (k0..k0+3, P/2) when SIDE.  The phases of tap
-// row / column 0 are exactly 1, so their products are plain sums.
-template <int NK, bool SIDE>
-__device__ __forceinline__ void gw_project_run(float (&gw)[4][NK * NK], const v4f (&dr)[4], const v4f (&di)[4], int k,
-                                               int l0, const float2 *tw) {
-  if constexpr (!SIDE) {
-    float2 u[NK], v[4][NK];
+template <int NK, int IMG, bool GAUSS, bool SIDE>
+__device__ __forceinline__ void gw_rows(const SpecLayout &G, const SpecLayout &X, const float2 *__restrict__ tw,
+                                        float *__restrict__ part, float2 *stage, int B, int S, int C, int P, int k,
+                                        int l_lo, int l_hi, int sbase, int cbase, int chunk) {
+  using St = GwStage<IMG>;
+  constexpr int LB = St::LB, RS = St::RS, LP = LB / 2, R = gw_record(NK);
+  constexpr int SUB = LB / 8;  // 2-column batches a wave takes of a stage
+  const int H = P / 2, tid = threadIdx.x;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int mrow = lane & 15, kq = lane >> 4;
+  const int sq = (wave >> 1) & 1, cq = wave & 1, bg = wave >> 2;
+
+  // this thread's pieces: plane row r of G and of X, image i of the stage, columns 2 j, 2 j + 1
+  // of rows k and -k (SIDE: rows l and l + P/2 of the Nyquist column)
+  const int j = tid % LP, r = (tid / LP) & 31, i = tid / (LP * 32);
+  const bool paired = SIDE || (k != 0 && k != H);
+  const long long gp = min(sbase + r, S - 1), xp = min(cbase + r, C - 1);
+  const float2 *gb, *xb;
+  long long gimg, ximg, row1;  // plane strides of an image; second row relative to the first
+  if constexpr (SIDE) {
+    gb = G.side + gp * G.sps, xb = X.side + xp * X.sps;
+    gimg = (long long)S * G.sps, ximg = (long long)C * X.sps, row1 = H;
+  } else {
+    gb = G.main + gp * G.ps + k * G.rs, xb = X.main + xp * X.ps + k * X.rs;
+    gimg = (long long)S * G.ps, ximg = (long long)C * X.ps, row1 = 0;
+  }
+  const long long grow = SIDE ? row1 : (paired ? (long long)(P - 2 * k) * G.rs : 0);
+  const long long xrow = SIDE ? row1 : (paired ? (long long)(P - 2 * k) * X.rs : 0);
+  const int halves = (B + IMG - 1) / IMG;
+  float4 pre[4];
+  int ll = l_lo, lh = 0;          // load cursor: column, image group
+  int held_l = l_lo, held_h = 0;  // the stage that pre holds
+  auto load = [&]() {
+    held_l = ll, held_h = lh;
+    const int l = ll + 2 * j, b = lh * IMG + i;
+    const long long lo = min(l, H - 2), bo = min(b, B - 1);
+    const float2 *g = gb + bo * gimg + lo, *x = xb + bo * ximg + lo;
+    pre[0] = *reinterpret_cast<const float4 *>(g);
+    pre[1] = *reinterpret_cast<const float4 *>(g + grow);
+    pre[2] = *reinterpret_cast<const float4 *>(x);
+    pre[3] = *reinterpret_cast<const float4 *>(x + xrow);
+  };
+  auto put = [&](int buf) {
+    float2 *d = stage + buf * St::BUF + (i * 64 + r) * RS + 2 * j;
+    float4 v[4] = {pre[0], pre[1], pre[2], pre[3]};
+    if (held_l + LB > l_hi || (held_h + 1) * IMG > B || !paired) {  // a stage with absent columns, images or row -k
+      const bool on = held_l + 2 * j < l_hi && held_h * IMG + i < B;
 #pragma unroll
-    for (int a = 1; a < NK; ++a) u[a] = tw[k * a];
+      for (int e = 0; e < 4; ++e) {
+        const bool c = (e & 1) ? on && paired : on;
+        v[e] = make_float4(c ? v[e].x : 0.f, c ? v[e].y : 0.f, c ? v[e].z : 0.f, c ? v[e].w : 0.f);
+      }
+    }
+    *reinterpret_cast<float4 *>(d) = v[0];
+    *reinterpret_cast<float4 *>(d + LB) = v[1];
+    *reinterpret_cast<float4 *>(d + 32 * RS) = v[2];
+    *reinterpret_cast<float4 *>(d + 32 * RS + LB) = v[3];
+  };
+  auto advance = [&]() {  // past the last stage the cursor stays on valid addresses (load clamps the column)
+    if (++lh == halves) lh = 0, ll += LB;
+  };
+
+  float ep[NK][4], eq[NK][4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
+  for (int b = 0; b < NK; ++b)
 #pragma unroll
-      for (int b = 1; b < NK; ++b) v[q][b] = tw[(l0 + q) * b];
+    for (int e = 0; e < 4; ++e) ep[b][e] = eq[b][e] = 0.f;
+
+  v4f t1[2][2], t2[2][2], t3[2][2];  // [row][column]; D = (t1, t2) without GAUSS
+  // products of the stage's images with this wave's columns 2 u, 2 u + 1; FIRST: the sums start here
+  auto multiply = [&](auto first, const float2 *st, int images) __attribute__((always_inline)) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int step = 0; step < IMG / 4; ++step) {
+      if (step > 0 && 4 * step >= images) break;  // no such images
+      const float2 *ga = st + ((4 * step + kq) * 64 + sq * 16 + mrow) * RS;
+      const float2 *xa = st + ((4 * step + kq) * 64 + 32 + cq * 16 + mrow) * RS;
+      const bool start = decltype(first)::value && step == 0;
+      const v4f zero = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int b = 0; b < NK; ++b) {
-        float ex, ey;  // E_b = sum_q D_q conj(v_qb)
-        if (b == 0) {
-          ex = (dr[0][j] + dr[1][j]) + (dr[2][j] + dr[3][j]);
-          ey = (di[0][j] + di[1][j]) + (di[2][j] + di[3][j]);
-        } else {
-          ex = ey = 0.f;
+      for (int e = 0; e < 2; ++e) {
+        const float4 g4 = *reinterpret_cast<const float4 *>(ga + e * LB);
+        const float4 x4 = *reinterpret_cast<const float4 *>(xa + e * LB);
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            ex = fmaf(dr[q][j], v[q][b].x, ex);
-            ex = fmaf(di[q][j], v[q][b].y, ex);
-            ey = fmaf(di[q][j], v[q][b].x, ey);
-            ey = fmaf(-dr[q][j], v[q][b].y, ey);
+        for (int q = 0; q < 2; ++q) {
+          const float gr = q ? g4.z : g4.x, gi = q ? g4.w : g4.y, xr = q ? x4.z : x4.x, xi = q ? x4.w : x4.y;
+          if constexpr (GAUSS) {
+            // Gauss's form: t1 = sum Gr Xr, t2 = sum Gi Xi, t3 = sum (Gr + Gi)(Xr - Xi)
+            t1[e][q] = mfma4(gr, xr, start ? zero : t1[e][q]);
+            t2[e][q] = mfma4(gi, xi, start ? zero : t2[e][q]);
+            t3[e][q] = mfma4(gr + gi, xr - xi, start ? zero : t3[e][q]);
+          } else {  // re = Gr Xr + Gi Xi, im = Gi Xr - Gr Xi
+            t1[e][q] = mfma4(gr, xr, start ? zero : t1[e][q]);
+            t2[e][q] = mfma4(gi, xr, start ? zero : t2[e][q]);
+            t1[e][q] = mfma4(gi, xi, t1[e][q]);
+            t2[e][q] = mfma4(-gr, xi, t2[e][q]);
           }
         }
-        gw[j][b] += ex;
-#pragma unroll
-        for (int a = 1; a < NK; ++a) gw[j][a * NK + b] = fmaf(ey, u[a].y, fmaf(ex, u[a].x, gw[j][a * NK + b]));
       }
-  } else {
-    float2 u[4][NK];
+    }
+  };
+  // the finished D of columns l, l + 1 (wave-uniform; zeros were staged past l_hi)
+  auto project = [&](int l) __attribute__((always_inline)) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
+    for (int q = 0; q < 2; ++q) {
+      float zc[NK], zs[NK];
+      const int lq = min(l + q, H - 1);
+      int at = 0;  // l b mod P
 #pragma unroll
-      for (int a = 1; a < NK; ++a) u[q][a] = tw[(k + q) * a];
+      for (int b = 1; b < NK; ++b) {
+        at += lq;
+        at -= at >= P ? P : 0;
+        const float2 z = tw[at];
+        zc[b] = z.x, zs[b] = z.y;
+      }
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+      for (int e = 0; e < 4; ++e) {
+        float re[2], im[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const float a1 = t1[h][q][e], a2 = t2[h][q][e];
+          if constexpr (GAUSS) {
+            re[h] = a1 + a2, im[h] = (t3[h][q][e] - a1) + a2;
+          } else {
+            re[h] = a1, im[h] = a2;
+          }
+        }
+        const float pr = re[0] + re[1], pi = im[0] + im[1], qr = re[0] - re[1], qi = im[0] - im[1];
+        if constexpr (SIDE) {  // EP_a alone, the pair's sum or difference by the parity of a
+          ep[0][e] += pr;
+#pragma unroll
+          for (int b = 1; b < NK; ++b) {
+            ep[b][e] = fmaf((b & 1) ? qr : pr, zc[b], ep[b][e]);
+            ep[b][e] = fmaf((b & 1) ? qi : pi, zs[b], ep[b][e]);
+          }
+        } else {
+          ep[0][e] += pr;
+          if (NK > 1) eq[0][e] += qi;
+#pragma unroll
+          for (int b = 1; b < NK; ++b) {
+            ep[b][e] = fmaf(pi, zs[b], fmaf(pr, zc[b], ep[b][e]));
+            eq[b][e] = fmaf(-qr, zs[b], fmaf(qi, zc[b], eq[b][e]));
+          }
+        }
+      }
+    }
+  };
+
+  load();
+  put(0);
+  advance();
+  load();
+  __syncthreads();
+  int buf = 0;
+  for (int cl = l_lo; cl < l_hi; cl += LB)
+    for (int ch = 0; ch < halves; ++ch) {
+      // the next stage into the other buffer (read last a stage ago), the loads of the one after
+      advance();
+      put(buf ^ 1);
+      load();
+      const float2 *st = stage + buf * St::BUF + bg * (LB / 4);
+      if constexpr (IMG == 4) {  // all images are in the stage; the wave's columns go two at a time
+        for (int u = 0; u < SUB; ++u) {
+          multiply(std::true_type{}, st + 2 * u, B);
+          project(cl + bg * (LB / 4) + 2 * u);
+        }
+      } else {
+        if (ch == 0)
+          multiply(std::true_type{}, st, B);
+        else
+          multiply(std::false_type{}, st, B - ch * IMG);
+        if (ch + 1 == halves) project(cl + bg * (LB / 4));
+      }
+      buf ^= 1;
+      __syncthreads();
+    }
+
+  // the four column quarters' sums, added in order by the waves of quarter 0
+  float *red = reinterpret_cast<float *>(stage);
+  const int slot = (wave & 3) * 64 + lane;
+  if (bg > 0) {
+    float *d = red + (bg - 1) * 256 * 8 * NK + slot;
+#pragma unroll
+    for (int b = 0; b < NK; ++b)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) d[(b * 8 + e) * 256] = ep[b][e], d[(b * 8 + 4 + e) * 256] = eq[b][e];
+  }
+  __syncthreads();
+  if (bg > 0) return;
+#pragma unroll
+  for (int g = 0; g < 3; ++g) {
+    const float *d = red + g * 256 * 8 * NK + slot;
+#pragma unroll
+    for (int b = 0; b < NK; ++b)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) ep[b][e] += d[(b * 8 + e) * 256], eq[b][e] += d[(b * 8 + 4 + e) * 256];
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int os = sbase + sq * 16 + 4 * kq + e, oc = cbase + cq * 16 + mrow;
+    if (os >= S || oc >= C) continue;
+    float *p = part + (((long long)chunk * S + os) * C + oc) * R;
+#pragma unroll
+    for (int b = 0; b < NK; ++b) {
+      p[b] = ep[b][e];
+      if (NK > 1) p[NK + b] = eq[b][e];
+    }
+  }
+}
+
+// Chunks: row pairs k = 0..P/2, then the Nyquist column, each in `ls` column ranges.
+template <int NK, int IMG, bool GAUSS>
+__global__ __launch_bounds__(kGwThreads) void k_full_gw(SpecLayout G, SpecLayout X, const float2 *__restrict__ tw,
+                                                        float *__restrict__ part, int B, int S, int C, int P,
+                                                        int ls) {
+  extern __shared__ float2 gw_lds[];
+  const int H = P / 2;
+  const int cblocks = (C + 31) / 32, tiles = ((S + 31) / 32) * cblocks;
+  const int blk = xcd_remap(blockIdx.x, gridDim.x);
+  const int chunk = blk / tiles, tile = blk - chunk * tiles;
+  const int k = chunk / ls, range = chunk - k * ls;
+  // whole stages a range
+  const int nl = (H + GwStage<IMG>::LB - 1) / GwStage<IMG>::LB;
+  const int l_lo = range * nl / ls * GwStage<IMG>::LB, l_hi = min(H, (range + 1) * nl / ls * GwStage<IMG>::LB);
+  const int sbase = (tile / cblocks) * 32, cbase = (tile % cblocks) * 32;
+  if (k <= H)
+    gw_rows<NK, IMG, GAUSS, false>(G, X, tw, part, gw_lds, B, S, C, P, k, l_lo, l_hi, sbase, cbase, chunk);
+  else
+    gw_rows<NK, IMG, GAUSS, true>(G, X, tw, part, gw_lds, B, S, C, P, 0, l_lo, l_hi, sbase, cbase, chunk);
+}
+
+// dL/dw from the partial sums: a workgroup owns PP (s, c) pairs; its 256 / PP thread groups
+// take the chunks in turn, apply the row phases, and their sums are added in order.  PP = 8
+// where 32 would leave few workgroups (64 -> 64 channels: 128 workgroups, 40 us).
+template <int NK, int PP>
+__global__ __launch_bounds__(256) void k_full_gw_reduce(const float *__restrict__ part, const float2 *__restrict__ tw,
+                                                        float *__restrict__ gw, long long pairs, int P, int ls) {
+  constexpr int T = NK * NK, R = gw_record(NK);
+  constexpr int GR = 256 / PP;
+  __shared__ float red[GR][PP][T + 1];
+  const int H = P / 2, o = threadIdx.x % PP, w = threadIdx.x / PP, chunks = (H + 2) * ls;
+  const long long i = (long long)blockIdx.x * PP + o, ii = i < pairs ? i : pairs - 1;
+  float acc[T];
+#pragma unroll
+  for (int t = 0; t < T; ++t) acc[t] = 0.f;
+#pragma unroll 4
+  for (int c = w; c < chunks; c += GR) {
+    const float *p = part + ((long long)c * pairs + ii) * R;
+    float v[R];
+#pragma unroll
+    for (int e = 0; e < R; ++e) v[e] = p[e];
+    const int k = c / ls;
+    if (k <= H) {
 #pragma unroll
       for (int a = 0; a < NK; ++a) {
-        float f;  // Re F_a = Re sum_q D_q conj(u_qa)
-        if (a == 0) {
-          f = (dr[0][j] + dr[1][j]) + (dr[2][j] + dr[3][j]);
-        } else {
-          f = 0.f;
+        const float2 u = a ? tw[(k * a) % P] : make_float2(1.f, 0.f);
 #pragma unroll
-          for (int q = 0; q < 4; ++q) f = fmaf(di[q][j], u[q][a].y, fmaf(dr[q][j], u[q][a].x, f));
+        for (int b = 0; b < NK; ++b) {
+          acc[a * NK + b] = fmaf(u.x, v[b], acc[a * NK + b]);
+          if (a) acc[a * NK + b] = fmaf(u.y, v[R > 1 ? NK + b : 0], acc[a * NK + b]);
         }
-#pragma unroll
-        for (int b = 0; b < NK; ++b) gw[j][a * NK + b] += (b & 1) ? -f : f;
       }
-  }
-}
-
-// Position of a run of 4 bins, advanced one run at a time (no divisions on the way).
-struct GwRun {
-  int g, k, l0;  // run index; row k and first column l0 (row runs) or first row k (Nyquist runs)
-  __device__ void start(int g0, int nmain, int H) {
-    g = g0;
-    if (g < nmain) {
-      k = (4 * g) / H, l0 = 4 * g - k * H;
     } else {
-      k = 4 * (g - nmain), l0 = 0;
+#pragma unroll
+      for (int a = 0; a < NK; ++a)
+#pragma unroll
+        for (int b = 0; b < NK; ++b) acc[a * NK + b] += (b & 1) ? -v[a] : v[a];
     }
   }
-  __device__ void next(int nmain, int H) {
-    ++g;
-    if (g == nmain) {
-      k = 0, l0 = 0;
-    } else if (g > nmain) {
-      k += 4;
-    } else if ((l0 += 4) == H) {
-      l0 = 0, ++k;
-    }
-  }
-};
-
-// LDS staging of one step (4 batch rows, one run of 4 bins) for a 32 x 32 (s, c)
-// block: G rows [4][32][5] and X rows [4][32][5] complex, each (b, s) row holding the
-// run's 4 bins and one of padding.  Every element is loaded from memory once per
-// workgroup (the four waves read each operand row twice: waves 0/1 share s rows, 0/2
-// share c rows).
-constexpr int kGwStageRow = 5;
-// X rows start 8 elements (16 banks of 4 bytes) after the G rows: the staging writes of
-// a 16-lane group (8 rows of G and the same 8 rows of X) then fall on distinct banks
-// (with the two blocks a multiple of 32 banks apart every write was a 2-way conflict)
-constexpr int kGwStageUnit = 4 * 32 * kGwStageRow + 8;
-constexpr int kGwStageElems = 2 * kGwStageUnit;
-
-// EVEN: the batch takes an even number of 4-row steps (B rounded up to 4 is a multiple
-// of 8), which allows the run-by-run loop.
-template <int NK, bool EVEN>
-__global__ __launch_bounds__(256, 2) void k_full_gw(SpecLayout G, SpecLayout X, const float2 *__restrict__ twg,
-                                                 float *__restrict__ part, int B, int S, int C, int P,
-                                                 int runs_per_chunk) {
-  constexpr int T = NK * NK, SR = kGwStageRow, SE = kGwStageElems;
-  extern __shared__ float smem[];
-  float2 *tw = reinterpret_cast<float2 *>(smem);
-  float2 *stage = tw + gw_tw_elems<NK>(P);  // two buffers of SE
-  for (int i = threadIdx.x; i < NK * P; i += 256) tw[i] = twg[i % P];
+#pragma unroll
+  for (int t = 0; t < T; ++t) red[w][o][t] = acc[t];
   __syncthreads();
-
-  const int H = P / 2, nmain = P * H / 4, nrun = nmain + P / 4;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int mrow = lane & 15, kq = lane >> 4;
-  const int sblocks = (S + 31) / 32, cblocks = (C + 31) / 32;
-  const int blk = xcd_remap(blockIdx.x, gridDim.x);
-  const int tile = blk % (sblocks * cblocks), chunk = blk / (sblocks * cblocks);
-  const int sbase = (tile / cblocks) * 32, cbase = (tile % cblocks) * 32;
-  const int s0 = sbase + (wave >> 1) * 16, c0 = cbase + (wave & 1) * 16;
-  const int r_begin = chunk * runs_per_chunk, r_end = min(nrun, r_begin + runs_per_chunk);
-
-  // Cooperative loads: wave lb takes batch row b0 + lb of the step; lane (lr, unit)
-  // loads the run's 4 bins of G row sbase + lr (unit 0) or X row cbase + lr (unit 1).
-  // Per-lane bases and batch strides of both blocks, so that a step's address is one
-  // multiply-add.
-  const int lb = wave, unit = lane & 1, lr = lane >> 1;
-  const SpecLayout &L = unit ? X : G;
-  const long long row = unit ? min(cbase + lr, C - 1) : min(sbase + lr, S - 1);
-  const long long nch = unit ? C : S;
-  const float2 *mbase = L.main + row * L.ps, *sbase_p = L.side + row * L.sps;
-  const long long mbst = nch * L.ps, sbst = nch * L.sps, mrs = L.rs;
-
-  float gw[4][T];  // rows s0 + 4 (lane / 16) + j, column c0 + lane % 16
+  for (int e = threadIdx.x; e < PP * T; e += 256) {
+    const int oo = e / T, t = e - oo * T;
+    if ((long long)blockIdx.x * PP + oo >= pairs) break;
+    float s = red[0][oo][t];
 #pragma unroll
-  for (int j = 0; j < 4; ++j)
-#pragma unroll
-    for (int t = 0; t < T; ++t) gw[j][t] = 0.f;
-
-  // Two register sets hold the loads of the next two steps, so that the loads of step
-  // t + 2 are in flight while step t computes.  Past the chunk's last step the run is
-  // clamped and the load is not used: an unconditional load keeps the wait counts
-  // exact, so step t waits for its own loads only.
-  GwRun lrun;
-  lrun.start(r_begin, nmain, H);
-  int lb0 = 0;  // load cursor: run lrun, batch rows lb0..lb0+3
-  auto load_next = [&](float4(&r)[2]) {
-    const long long bc = min(lb0 + lb, B - 1);
-    const bool side = lrun.g >= nmain;
-    const int gk = min(lrun.k, side ? P - 4 : P - 1);  // in range past the last run
-    const float2 *a = side ? sbase_p + bc * sbst + gk : mbase + bc * mbst + gk * mrs + lrun.l0;
-    const float4 *a4 = reinterpret_cast<const float4 *>(a);
-    r[0] = a4[0], r[1] = a4[1];
-    lb0 += 4;
-    if (lb0 >= B) lb0 = 0, lrun.next(nmain, H);
-  };
-  float4 ra[2], rb[2];
-  load_next(ra);
-  load_next(rb);
-  // Up to 3 x 3 taps and with the run-by-run loop, Gauss's form of the complex
-  // product: t1 = sum Gr Xr, t2 = sum Gi Xi and t3 = sum (Gr + Gi)(Xr - Xi) over the
-  // batch, three matrix products per bin instead of four; the run's D = G conj(X) is
-  // then re = t1 + t2, im = t3 - t1 + t2.  (Elsewhere the third accumulator would
-  // cost occupancy or spill, and four products are kept.)
-  constexpr bool kGauss = EVEN && NK <= 3;
-  v4f t1[4], t2[4], t3[4], dr[4], di[4];
-  GwRun crun;
-  crun.start(r_begin, nmain, H);
-  int b0 = 0;  // compute cursor
-  // Stage the registers r (loaded two steps ago) into LDS buffer buf, then this step's
-  // products (4 batch rows of the run crun).
-  auto stage_and_multiply = [&](float4(&r)[2], int buf) __attribute__((always_inline)) {
-    // (the barrier below also ends every wave's reads of this buffer two steps ago)
-    {
-      float2 *d = stage + buf * SE + unit * kGwStageUnit + (lb * 32 + lr) * SR;
-      if (b0 + lb < B) {
-        d[0] = make_float2(r[0].x, r[0].y), d[1] = make_float2(r[0].z, r[0].w);
-        d[2] = make_float2(r[1].x, r[1].y), d[3] = make_float2(r[1].z, r[1].w);
-      } else {  // batch rows past the end add nothing
-        d[0] = d[1] = d[2] = d[3] = make_float2(0.f, 0.f);
-      }
-    }
-    __syncthreads();
-    load_next(r);
-    const float2 *ag = stage + buf * SE + (kq * 32 + (s0 - sbase) + mrow) * SR;
-    const float2 *ax = stage + buf * SE + kGwStageUnit + (kq * 32 + (c0 - cbase) + mrow) * SR;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const float2 g2 = ag[q], x2 = ax[q];
-      if constexpr (kGauss) {
-        t1[q] = mfma4(g2.x, x2.x, t1[q]);
-        t2[q] = mfma4(g2.y, x2.y, t2[q]);
-        t3[q] = mfma4(g2.x + g2.y, x2.x - x2.y, t3[q]);
-      } else {  // D = G conj(X):  re = Gr Xr + Gi Xi,  im = Gi Xr - Gr Xi
-        dr[q] = mfma4(g2.x, x2.x, dr[q]);
-        dr[q] = mfma4(g2.y, x2.y, dr[q]);
-        di[q] = mfma4(g2.y, x2.x, di[q]);
-        di[q] = mfma4(-g2.x, x2.y, di[q]);
-      }
-    }
-    b0 += 4;
-  };
-  auto clear_sums = [&]() __attribute__((always_inline)) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      if constexpr (kGauss)
-        t1[q] = t2[q] = t3[q] = v4f{0.f, 0.f, 0.f, 0.f};
-      else
-        dr[q] = di[q] = v4f{0.f, 0.f, 0.f, 0.f};
-    }
-  };
-  auto finish_run = [&]() __attribute__((always_inline)) {  // project the run onto the taps
-    if constexpr (kGauss) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        dr[q] = t1[q] + t2[q];
-        di[q] = (t3[q] - t1[q]) + t2[q];
-      }
-    }
-    if (crun.g >= nmain)
-      gw_project_run<NK, true>(gw, dr, di, crun.k, crun.l0, tw);
-    else
-      gw_project_run<NK, false>(gw, dr, di, crun.k, crun.l0, tw);
-    b0 = 0;
-    crun.next(nmain, H);
-  };
-  const int spr = (B + 3) / 4;  // steps per run
-  if constexpr (EVEN) {
-    // An even step count per run (the launcher checks): a run is whole pairs of steps,
-    // so the register sets alternate inside it, and the sums are cleared before and
-    // projected after it, with no branch on them inside the step loop.
-    for (int g = r_begin; g < r_end; ++g) {
-      clear_sums();
-      for (int t = 0; t < spr; t += 2) {  // one path round the loop keeps the wait counts exact
-        stage_and_multiply(ra, 0);
-        stage_and_multiply(rb, 1);
-      }
-      finish_run();
-    }
-  } else {
-    auto step = [&](float4(&r)[2], int buf) __attribute__((always_inline)) {
-      if (b0 == 0) clear_sums();
-      stage_and_multiply(r, buf);
-      if (b0 >= B) finish_run();
-    };
-    const int nsteps = max(0, r_end - r_begin) * spr;
-    int t = 0;
-    for (; t + 1 < nsteps; t += 2) {  // one path round the loop keeps the wait counts exact
-      step(ra, 0);
-      step(rb, 1);
-    }
-    if (t < nsteps) step(ra, 0);
+    for (int q = 1; q < GR; ++q) s += red[q][oo][t];
+    gw[((long long)blockIdx.x * PP + oo) * T + t] = s;
   }
-  // this chunk's partial sums
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int os = s0 + 4 * kq + j, oc = c0 + mrow;
-    if (os >= S || oc >= C) continue;
-    float *p = part + (((long long)chunk * S + os) * C + oc) * T;
-#pragma unroll
-    for (int t = 0; t < T; ++t) p[t] = gw[j][t];
-  }
-}
-
-// dL/dw = sum over chunks in a fixed order: a workgroup owns 64 outputs; its four
-// waves sum the chunks congruent to 0, 1, 2, 3 mod 4 (four accumulators each, chunk
-// c into accumulator (c / 4) mod 4), and the 16 partial sums are added in order.
-__global__ __launch_bounds__(256) void k_full_gw_reduce(const float *__restrict__ part, float *__restrict__ gw,
-                                                        long long n, int chunks) {
-  __shared__ float red[4][64];
-  const int o = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const long long i = (long long)blockIdx.x * 64 + o;
-  const long long ii = i < n ? i : n - 1;
-  float acc[4] = {0.f, 0.f, 0.f, 0.f};
-  int c = w;
-  for (; c + 12 < chunks; c += 16) {
-#pragma unroll
-    for (int u = 0; u < 4; ++u) acc[u] += part[(long long)(c + 4 * u) * n + ii];
-  }
-  for (int u = 0; c < chunks; c += 4, ++u) acc[u] += part[(long long)c * n + ii];
-  red[w][o] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
-  __syncthreads();
-  if (w == 0 && i < n) gw[i] = (red[0][o] + red[1][o]) + (red[2][o] + red[3][o]);
 }
 
 // Weights rearranged for the contraction, zero-padded: wt[kd][nd][tap] of
@@ -885,6 +898,19 @@ static bool dispatch_nk(int nk, F &&f) {
 
 bool full_kernel_size_supported(int nk) { return nk >= 1 && nk <= 5; }
 
+// Column ranges each row pair is cut into: about 1024 workgroups (four a compute unit) and
+// whole stages.
+static int gw_ranges(int B, int S, int C, int P) {
+  const int lb = B <= 4 ? GwStage<4>::LB : GwStage<8>::LB, H = P / 2;
+  const long long tiles = (long long)((S + 31) / 32) * ((C + 31) / 32), wgs = tiles * (H + 2);
+  const long long ls = (1024 + wgs - 1) / wgs;
+  return (int)std::min<long long>(ls, (H + lb - 1) / lb);
+}
+// Floats of the dL/dw pass's partial sums.
+size_t full_gw_part_floats(int B, int S, int C, int P, int nk) {
+  return (size_t)(P / 2 + 2) * gw_ranges(B, S, C, P) * S * C * gw_record(nk);
+}
+
 bool full_launch_fits(int B, int Cin, int Cout, int P, int nk) {
   if (P % 8 != 0 || B < 1 || B > 65535 * 16) return false;
   const long long nrun = (long long)P * (P / 2) / 4 + P / 4;
@@ -895,8 +921,8 @@ bool full_launch_fits(int B, int Cin, int Cout, int P, int nk) {
   if (nwg_run * ((Cin + kCtOut - 1) / kCtOut) * nbt >= lim) return false;
   // dL/dw: tiles of 32 x 32 (s, c) times bin chunks, and the fixed-order reduction
   const long long tiles = (long long)((Cout + 31) / 32) * ((Cin + 31) / 32);
-  if (tiles * full_gw_chunks(B, Cout, Cin, P, nk) >= lim) return false;
-  if (((long long)Cout * Cin * nk * nk + 63) / 64 >= lim) return false;
+  if (tiles * (P / 2 + 2) * gw_ranges(B, Cout, Cin, P) >= lim) return false;
+  if (((long long)Cout * Cin * nk * nk + 31) / 32 >= lim) return false;
   return true;
 }
 
@@ -983,50 +1009,44 @@ hipError_t launch_full_contract(bool gx, int nk, SpecLayout in, const float *wt,
   return err;
 }
 
-// Bin chunks of the dL/dw pass: about 8192 workgroups, so that the workgroups running
-// at one time on an XCD are the tiles of one or two short chunks and share the spectra
-// they read through L2, and at most 97 runs (388 bins) per chunk; at most 512 chunks of
-// partial sums.  At 512 pixels and 256 channels (64 tiles) the pass took 13.3-13.8 ms
-// with 97 or 129 runs per chunk, 15.1 ms with 65, 17-22 ms with 128 (two whole rows:
-// every chunk starts at the same column), 22-24 ms with 161 or 193, and 15-19 ms, uneven
-// from run to run and with 2.3 times the HBM reads, with the 257 that 8192 workgroups
-// alone give.
-constexpr int kGwMaxRunsPerChunk = 97;
-int full_gw_chunks(int B, int S, int C, int P, int nk) {
-  (void)B, (void)nk;
-  const int nrun = P * (P / 2) / 4 + P / 4;
-  const int tiles = ((S + 31) / 32) * ((C + 31) / 32);
-  int chunks = std::max((8192 + tiles - 1) / tiles, (nrun + kGwMaxRunsPerChunk - 1) / kGwMaxRunsPerChunk);
-  if (chunks > 512) chunks = 512;
-  if (chunks > nrun) chunks = nrun;
-  if (chunks < 1) chunks = 1;
-  return chunks;
-}
-
 hipError_t launch_full_gw(int nk, SpecLayout G, SpecLayout X, const float2 *tw, float *part, float *gw, int B, int S,
                           int C, int P, hipStream_t s) {
   if (P % 8 != 0) return hipErrorInvalidValue;
-  const int nrun = P * (P / 2) / 4 + P / 4;
-  const int chunks = full_gw_chunks(B, S, C, P, nk);
-  const int runs_per_chunk = (nrun + chunks - 1) / chunks;
-  const int tiles = ((S + 31) / 32) * ((C + 31) / 32);
+  const int ls = gw_ranges(B, S, C, P);
+  const long long tiles = (long long)((S + 31) / 32) * ((C + 31) / 32), grid = tiles * (P / 2 + 2) * ls;
+  const long long pairs = (long long)S * C;
+  const int pp = pairs < 32 * 1024 ? 8 : 32;
+  const long long rgrid = (pairs + pp - 1) / pp;
+  if (grid >= (1LL << 31) || rgrid >= (1LL << 31)) return hipErrorInvalidValue;
   hipError_t err = hipErrorInvalidValue;
   dispatch_nk(nk, [&](auto nc) {
     constexpr int NK = decltype(nc)::value;
-    const size_t lds = ((size_t)gw_tw_elems<NK>(P) + 2 * kGwStageElems) * sizeof(float2);
-    if (lds > 65536) return;  // (P <= 1024, n <= 5 stays within 60 KB)
-    if (((B + 3) / 4) % 2 == 0)
-      err = timed_launch("full_gw", k_full_gw<NK, true>, dim3((unsigned)(tiles * chunks)), dim3(256), lds, s, G, X, tw,
-                         part, B, S, C, P, runs_per_chunk);
+    auto go = [&](auto ic) {
+      constexpr int IMG = decltype(ic)::value;
+      // Gauss's three products pay from two 4-image steps on; with more taps the third
+      // accumulator would spill
+      constexpr bool kGauss = IMG == 8 && NK <= 3;
+      constexpr size_t lds = (size_t)2 * GwStage<IMG>::BUF * sizeof(float2);
+      static_assert(lds <= 160 * 1024 && lds >= (size_t)3 * 256 * 8 * NK * sizeof(float), "dL/dw: LDS");
+      static const hipError_t attr =
+          hipFuncSetAttribute(reinterpret_cast<const void *>(k_full_gw<NK, IMG, kGauss>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      err = attr;
+      if (err != hipSuccess) return;
+      err = timed_launch("full_gw", k_full_gw<NK, IMG, kGauss>, dim3((unsigned)grid), dim3(kGwThreads), lds, s, G, X,
+                         tw, part, B, S, C, P, ls);
+    };
+    if (B <= 4)
+      go(std::integral_constant<int, 4>{});
     else
-      err = timed_launch("full_gw", k_full_gw<NK, false>, dim3((unsigned)(tiles * chunks)), dim3(256), lds, s, G, X,
-                         tw, part, B, S, C, P, runs_per_chunk);
+      go(std::integral_constant<int, 8>{});
+    if (err != hipSuccess) return;
+    err = pp == 8 ? timed_launch("full_gw_reduce", k_full_gw_reduce<NK, 8>, dim3((unsigned)rgrid), dim3(256), 0, s,
+                                 part, tw, gw, pairs, P, ls)
+                  : timed_launch("full_gw_reduce", k_full_gw_reduce<NK, 32>, dim3((unsigned)rgrid), dim3(256), 0, s,
+                                 part, tw, gw, pairs, P, ls);
   });
-  if (err != hipSuccess) return err;
-  const long long n = (long long)S * C * nk * nk;
-  const long long g = (n + 63) / 64;
-  if (g >= (1LL << 31)) return hipErrorInvalidValue;
-  return timed_launch("full_gw_reduce", k_full_gw_reduce, dim3((unsigned)g), dim3(256), 0, s, part, gw, n, chunks);
+  return err;
 }
 
 }  // namespace fdc

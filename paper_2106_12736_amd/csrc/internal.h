@@ -210,7 +210,7 @@ hipError_t launch_tail_bwd(int na, int ma, int mb, int ja, int jb, const float *
 // floats: KD = Cin, ND = Cout forward (gx = false); KD = Cout, ND = Cin for dL/dX.
 bool full_kernel_size_supported(int nk);
 size_t full_weight_floats(int KD, int ND, int nk);
-int full_gw_chunks(int B, int S, int C, int P, int nk);
+size_t full_gw_part_floats(int B, int S, int C, int P, int nk);
 // Whether every Full FDC launch of a layer (both contractions, dL/dw and its reduction)
 // fits its grid limits.
 bool full_launch_fits(int B, int Cin, int Cout, int P, int nk);
