@@ -326,7 +326,14 @@ constexpr int stockham_ns(int p) {  // product of the radices before pass p
 //   kLdsPad:   one complex value of padding after every 32, which breaks up the
 //              power-of-two strides of the row kernels' exchanges (element stride 1).
 // lds_size<LAYOUT>(n) complex values hold indices [0, n).
-enum { kLdsPlain = 0, kLdsXor = 1, kLdsPad = 2 };
+//   kLdsSeq:   element e of a short row sequence (N <= 128, es = 1) at base + e + e / 8 (e / 16
+//              at 128 points): the exchanges' writes (16 lanes over 32 banks a cycle) and reads
+//              (32 lanes over 64 banks) are free of conflicts when sequences are row_slot<N>()
+//              apart;
+//   kLdsPlane: element e of a column of an image plane at base + plane_at(e, es): rows of
+//              es = plane_ld complex values with plane_pad of padding after every 8, which does
+//              the same for column transforms in place (see plane.h).
+enum { kLdsPlain = 0, kLdsXor = 1, kLdsPad = 2, kLdsSeq = 3, kLdsPlane = 4 };
 template <int LAYOUT>
 __device__ __forceinline__ int lds_phys(int i) {
   if constexpr (LAYOUT == kLdsPlain) return i;
@@ -336,6 +343,21 @@ __device__ __forceinline__ int lds_phys(int i) {
 template <int LAYOUT>
 __host__ __device__ constexpr int lds_size(int n) {
   return LAYOUT == kLdsPad ? n + (n >> 5) + 1 : (n + 31) & ~31;
+}
+
+__host__ __device__ constexpr int plane_pad(int ld) { return ld % 16 == 8 ? 8 : 4; }
+__host__ __device__ constexpr int plane_at(int row, int ld) { return row * ld + (row >> 3) * plane_pad(ld); }
+// Slot of one N-point sequence in the kLdsSeq layout.
+template <int N>
+__host__ __device__ constexpr int row_slot() {
+  return N == 128 ? 144 : N + N / 8;
+}
+// Address of element e of a sequence at `base` with element stride es.
+template <int LAYOUT, int N>
+__device__ __forceinline__ int seq_at(int base, int e, int es) {
+  if constexpr (LAYOUT == kLdsSeq) return base + e + (e >> (N >= 128 ? 4 : 3));
+  else if constexpr (LAYOUT == kLdsPlane) return base + plane_at(e, es);
+  else return lds_phys<LAYOUT>(base + e * es);
 }
 
 // Barrier between the LDS writes and reads of an exchange.  WAVE: every
@@ -401,7 +423,7 @@ __device__ __forceinline__ void fft_seq(float2 (&v)[Cfg::E], int t, float2 *lds,
         const int rdq = FOLD_RQ ? rd0 + pad_offset(TPS * q) : (FOLD_RD ? lds_phys<LAYOUT>(base + j) : 0);
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-          float2 x = FOLD_RD ? lds[rdq + pad_offset(r * NR)] : lds[lds_phys<LAYOUT>(base + (j + r * NR) * es)];
+          float2 x = FOLD_RD ? lds[rdq + pad_offset(r * NR)] : lds[seq_at<LAYOUT, N>(base, j + r * NR, es)];
           if (r > 0) {
             float2 w = tw[r * k * (N / (NS * R)) * tws];
             if (DIR > 0) w.y = -w.y;
@@ -436,7 +458,7 @@ __device__ __forceinline__ void fft_seq(float2 (&v)[Cfg::E], int t, float2 *lds,
           for (int r = 0; r < R; ++r) lds[w0 + pad_offset(r * NS)] = a[q + BPT * r];
         } else {
 #pragma unroll
-          for (int r = 0; r < R; ++r) lds[lds_phys<LAYOUT>(base + (jo + r * NS) * es)] = a[q + BPT * r];
+          for (int r = 0; r < R; ++r) lds[seq_at<LAYOUT, N>(base, jo + r * NS, es)] = a[q + BPT * r];
         }
       }
       lds_barrier<WAVE>();

@@ -35,6 +35,7 @@
 #include "device.h"
 #include "fft.h"
 #include "internal.h"
+#include "plane.h"
 
 #include <hip/hip_runtime.h>
 
@@ -44,156 +45,29 @@ namespace fdc {
 
 extern __shared__ float2 t_lds[];
 
-namespace tail {
 
-// Every transform of the tail uses the column plans: E = 8 elements per thread.
-template <int N>
-using Plan = ColCfg<N>;
-
-// LDS planes: `rows` rows of ld complex values, ld > L (spare columns give idle
-// lanes somewhere harmless to exchange through) and odd (a column walked by
-// consecutive rows spreads over the banks).
-__host__ __device__ constexpr int plane_ld(int L) { return (L % 2 == 1) ? L + 2 : L + 1; }
-
-template <int N, int M>
-__device__ __forceinline__ int kept(int mrow) {
-  return mrow < M / 2 ? mrow : mrow + (N - M);
-}
-
-__device__ __forceinline__ float weight(int l, int n, float alpha, float beta) {
-  return (l == 0 || 2 * l == n) ? alpha : alpha * beta;
-}
-
-// Bin (plane, row, l) of a spectrum (SpecLayout) in HBM.
-__device__ __forceinline__ float2 *spec_at(const SpecLayout &s, long long plane, int row, int l, int L) {
-  return l < L - 1 ? s.main + plane * s.ps + (long long)row * s.rs + bin_off(s, l)
-                   : s.side + plane * s.sps + (long long)row * s.srs;
-}
-
-// Lane roles.  Row passes: t fastest (a wave reads whole rows).  Column passes:
-// the W = 64 / TPS columns of a wave fastest (a wave's global accesses are runs of
-// W consecutive bins of a row).
-template <int N>
-struct RowLanes {
-  static constexpr int TPS = Plan<N>::TPS, W = 64 / TPS;
-  int t, s, first;
-  __device__ RowLanes() {
-    const int lane = threadIdx.x & 63;
-    t = lane % TPS;
-    s = lane / TPS;
-    first = (threadIdx.x >> 6) * W;
-  }
-};
-template <int N>
-struct ColLanes {
-  static constexpr int TPS = Plan<N>::TPS, W = 64 / TPS;
-  int t, s, first;
-  __device__ ColLanes() {
-    const int lane = threadIdx.x & 63;
-    s = lane % W;
-    t = lane / W;
-    first = (threadIdx.x >> 6) * W;
-  }
-};
-
-// ----------------------------------------------------------------------------
-// row passes (pairs of real rows packed as one complex sequence z = a + i b)
-// ----------------------------------------------------------------------------
-// Packed inverse input of rows (r, r + 1): v[m] = A_k + i B_k at k = t + TPS m, the
-// Hermitian extensions of the two rows' first LIN bins weighted by c-weights (a1 at
-// l = 0 and N/2, a1 b1 elsewhere), with real-part semantics at l = 0 and N/2.
-template <int N, int LIN, class Bin>
-__device__ __forceinline__ void c2r_in(float2 (&v)[Plan<N>::E], Bin bin, int t, float a1, float b1) {
-  constexpr int TPS = Plan<N>::TPS, E = Plan<N>::E;
-#pragma unroll
-  for (int m = 0; m < E; ++m) {
-    const int k = t + TPS * m;
-    const bool upper = 2 * k > N;
-    const int kk = upper ? N - k : k;
-    const bool in = kk < LIN;
-    float2 a = bin(0, in ? kk : 0), b = bin(1, in ? kk : 0);
-    const bool edge = kk == 0 || 2 * kk == N;
-    const float w = in ? (edge ? a1 : a1 * b1) : 0.f;
-    a = cscale(a, w);
-    b = cscale(b, w);
-    if (edge) a.y = b.y = 0.f;
-    if (upper) a.y = -a.y, b.y = -b.y;
-    v[m] = make_float2(a.x - b.y, a.y + b.x);
-  }
-}
-
-// Forward transform output of a packed pair (held in registers, comb order) ->
-// the two rows' weighted bins k < LOUT: emit(row 0 or 1, k, value).
-template <int N, int LOUT, class Emit>
-__device__ __forceinline__ void r2c_out(const float2 (&v)[Plan<N>::E], float2 *scr, int sq, int t, float a2,
-                                        float b2, Emit emit) {
-  constexpr int TPS = Plan<N>::TPS, E = Plan<N>::E;
-  lds_barrier<true>();
-#pragma unroll
-  for (int m = 0; m < E; ++m) scr[lds_phys<kLdsPad>(sq * N + t + TPS * m)] = v[m];
-  lds_barrier<true>();
-  for (int k = t; k < LOUT; k += TPS) {
-    const float2 zk = scr[lds_phys<kLdsPad>(sq * N + k)];
-    const float2 zn = scr[lds_phys<kLdsPad>(sq * N + (k == 0 ? 0 : N - k))];
-    const float w = 0.5f * weight(k, N, a2, b2);
-    emit(0, k, make_float2((zk.x + zn.x) * w, (zk.y - zn.y) * w));
-    emit(1, k, make_float2((zk.y + zn.y) * w, (zn.x - zk.x) * w));
-  }
-}
-
-// ----------------------------------------------------------------------------
-// column passes (in place in an LDS plane)
-// ----------------------------------------------------------------------------
-// For every item (plane q < nq, column l < L): load(v, q, l, t, act) fills the
-// column, the N-point transform (direction DIR) runs through column l of plane(q),
-// store(v, q, l, t, act) takes the result.  Idle lanes (act = false) work on the
-// spare column L of plane 0 and must not store.
-template <int N, int DIR, int NT, class Load, class PlaneOf, class Store>
-__device__ __forceinline__ void col_pass(int nq, int L, const float2 *tw, int tws, Load load, PlaneOf plane,
-                                         Store store) {
-  using C = Plan<N>;
-  constexpr int SEQ = NT / C::TPS;
-  const ColLanes<N> ln;
-  const int items = nq * L;
-  for (int r0 = 0; r0 + ln.first < items; r0 += SEQ) {
-    const int it = r0 + ln.first + ln.s;
-    const bool act = it < items;
-    const int q = act ? it / L : 0, l = act ? it - (it / L) * L : L;
-    float2 v[C::E];
-    load(v, q, l, ln.t, act);
-    fft_seq<N, DIR, true, true, kLdsPlain, C>(v, ln.t, plane(q), l, plane_ld(L), tw, tws);
-    store(v, q, l, ln.t, act);
-  }
-}
-
-}  // namespace tail
-
-using namespace tail;
+using namespace plane;
 
 // Sizes of the LDS layout of the two tail kernels (complex values).
 template <int NA, int MA, int MB, int JA, int JB>
 struct TailGeom {
   static constexpr int LP = NA / 2 + 1;  // bins of the previous layer's output rows
   static constexpr int LA = MA / 2 + 1, LB = MB / 2 + 1;
-  static constexpr int ldA = plane_ld(LA), ldB = plane_ld(LB);
+  // leading dimensions of the planes, by the plan of their columns: TA, VA; XA, UA, GA; TB,
+  // VB; XB, UB, GB
+  static constexpr int ldT = plane_ld<NA>(LA), ldA = plane_ld<MA>(LA), ldC = plane_ld<MA>(LB),
+                       ldB = plane_ld<MB>(LB);
+  static constexpr int sT = plane_size(NA, ldT), sA = plane_size(MA, ldA), sC = plane_size(MA, ldC),
+                       sB = plane_size(MB, ldB);
   static constexpr int TW = twiddle_lds_elems<NA>();
-  // forward: TA [NA][ldA], XA [MA][ldA], UA[JA] [MA][ldA], TB[JA] [MA][ldB],
+  // forward: TA [NA][ldT], XA [MA][ldA], UA[JA] [MA][ldA], TB[JA] [MA][ldC],
   // XB[JA] [MB][ldB], UB[JA JB] [MB][ldB]
-  static constexpr int fTA = TW, fXA = fTA + NA * ldA, fUA = fXA + MA * ldA, fTB = fUA + JA * MA * ldA,
-                       fXB = fTB + JA * MA * ldB, fUB = fXB + JA * MB * ldB, fEnd = fUB + JA * JB * MB * ldB;
-  // backward: GB[JA JB] [MB][ldB], VB[JA] [MA][ldB], GA[JA] [MA][ldA], VA [NA][ldA]
-  static constexpr int bGB = TW, bVB = bGB + JA * JB * MB * ldB, bGA = bVB + JA * MA * ldB,
-                       bVA = bGA + JA * MA * ldA, bEnd = bVA + NA * ldA;
+  static constexpr int fTA = TW, fXA = fTA + sT, fUA = fXA + sA, fTB = fUA + JA * sA, fXB = fTB + JA * sC,
+                       fUB = fXB + JA * sB, fEnd = fUB + JA * JB * sB;
+  // backward: GB[JA JB] [MB][ldB], VB[JA] [MA][ldC], GA[JA] [MA][ldA], VA [NA][ldT]
+  static constexpr int bGB = TW, bVB = bGB + JA * JB * sB, bGA = bVB + JA * sC, bVA = bGA + JA * sA,
+                       bEnd = bVA + sT;
 };
-
-// Scratch of a row pass of `items` pairs of N-point rows with NT threads (padded
-// layout): one N-point sequence per slot, slots of whole waves up to NT / TPS.
-template <int N, int NT>
-__host__ __device__ constexpr int row_scratch(int items) {
-  constexpr int TPS = Plan<N>::TPS, W = 64 / TPS, SEQ = NT / TPS;
-  const int used = (items + W - 1) / W * W;
-  return lds_size<kLdsPad>((used < SEQ ? used : SEQ) * N);
-}
 
 // ----------------------------------------------------------------------------
 // forward
@@ -215,7 +89,8 @@ __global__ __launch_bounds__(NT) void k_tail_fwd(SpecLayout in, const float *__r
                                                  int C) {
   static_assert(JA % JL == 0, "channel groups of equal size");
   using G = TailGeom<NA, MA, MB, JL, JB>;
-  constexpr int LA = G::LA, LB = G::LB, ldA = G::ldA, ldB = G::ldB;
+  constexpr int LA = G::LA, LB = G::LB, ldT = G::ldT, ldA = G::ldA, ldC = G::ldC, ldB = G::ldB;
+  constexpr int sA = G::sA, sC = G::sC, sB = G::sB;
   constexpr int NFA = NA / 2 + 1, NFB = MA / 2 + 1, JG = JA / JL;
   float2 *tw = t_lds;
   stage_twiddles<NA>(tw, threadIdx.x, NT);
@@ -259,19 +134,20 @@ __global__ __launch_bounds__(NT) void k_tail_fwd(SpecLayout in, const float *__r
     for (int r0 = 0; r0 + ln.first < NA / 2; r0 += SEQ) {
       const int p = r0 + ln.first + ln.s;
       const bool act = p < NA / 2;
-      const int r = 2 * (act ? p : 0);
+      const int r = act ? p : 0;  // rows r and r + N/2
       float2 v[Plan<NA>::E];
       if constexpr (FIRST) {
         const float *xr = x + plane * NA * NA + (long long)r * NA;
 #pragma unroll
-        for (int m = 0; m < Plan<NA>::E; ++m) v[m] = make_float2(xr[ln.t + TPS * m], xr[NA + ln.t + TPS * m]);
+        for (int m = 0; m < Plan<NA>::E; ++m) v[m] = make_float2(xr[ln.t + TPS * m], xr[NA / 2 * NA + ln.t + TPS * m]);
       } else {
-        c2r_in<NA, NFA>(v, [&](int rr, int k) { return *spec_at(in, plane, r + rr, k, NFA); }, ln.t, a_in, 1.f);
-        fft_seq<NA, +1, true, true, kLdsPad, Plan<NA>>(v, ln.t, scr, (ln.first + ln.s) * NA, 1, tw, 1);
+        c2r_in<NA, NFA>(v, [&](int rr, int k) { return *spec_at(in, plane, r + rr * (NA / 2), k, NFA); }, ln.t, a_in, 1.f);
+        fft_seq<NA, +1, true, true, kLdsSeq, Plan<NA>>(v, ln.t, scr, (ln.first + ln.s) * row_slot<NA>(), 1, tw, 1);
       }
-      fft_seq<NA, -1, true, true, kLdsPad, Plan<NA>>(v, ln.t, scr, (ln.first + ln.s) * NA, 1, tw, 1);
-      r2c_out<NA, LA>(v, scr, ln.first + ln.s, ln.t, 1.f, 1.f, [&](int rr, int k, float2 val) {
-        if (act) TA[(r + rr) * ldA + k] = val;
+      fft_seq<NA, -1, true, true, kLdsSeq, Plan<NA>>(v, ln.t, scr, (ln.first + ln.s) * row_slot<NA>(), 1, tw, 1);
+      float2 *ta = TA + plane_at(r, ldT);
+      r2c_out<NA, LA>(v, scr + (ln.first + ln.s) * row_slot<NA>(), ln.t, 1.f, 1.f, [&](int rr, int k, float2 val) {
+        if (act) ta[rr * plane_at(NA / 2, ldT) + k] = val;
       });
     }
   }
@@ -283,7 +159,7 @@ __global__ __launch_bounds__(NT) void k_tail_fwd(SpecLayout in, const float *__r
         1, LA, tw, 1,
         [&](float2 (&v)[Plan<NA>::E], int, int l, int t, bool) {
 #pragma unroll
-          for (int m = 0; m < Plan<NA>::E; ++m) v[m] = TA[(t + Plan<NA>::TPS * m) * ldA + l];
+          for (int m = 0; m < Plan<NA>::E; ++m) v[m] = TA[plane_at(t + Plan<NA>::TPS * m, ldT) + l];
         },
         [&](int) { return TA; },
         [&](const float2 (&v)[Plan<NA>::E], int, int l, int t, bool act) {
@@ -293,7 +169,7 @@ __global__ __launch_bounds__(NT) void k_tail_fwd(SpecLayout in, const float *__r
             const int k = t + Plan<NA>::TPS * m;
             if (k < MA / 2 || k >= NA - MA / 2) {
               const int mrow = k < MA / 2 ? k : k - (NA - MA);
-              XA[mrow * ldA + l] = v[m];
+              XA[plane_at(mrow, ldA) + l] = v[m];
               if (JG == 1 || j0 == 0) *spec_at(saved_a, plane, mrow, l, LA) = v[m];
             }
           }
@@ -309,14 +185,14 @@ __global__ __launch_bounds__(NT) void k_tail_fwd(SpecLayout in, const float *__r
 #pragma unroll
         for (int m = 0; m < Plan<MA>::E; ++m) {
           const int mrow = t + Plan<MA>::TPS * m;
-          v[m] = cmul(XA[mrow * ldA + l], PC ? kpa[m] : kc[(long long)kept<NA, MA>(mrow) * NFA]);
+          v[m] = cmul(XA[plane_at(mrow, ldA) + l], PC ? kpa[m] : kc[(long long)kept<NA, MA>(mrow) * NFA]);
         }
       },
-      [&](int j) { return UA + j * MA * ldA; },
+      [&](int j) { return UA + j * sA; },
       [&](const float2 (&v)[Plan<MA>::E], int j, int l, int t, bool act) {
         if (!act) return;
 #pragma unroll
-        for (int m = 0; m < Plan<MA>::E; ++m) UA[j * MA * ldA + (t + Plan<MA>::TPS * m) * ldA + l] = v[m];
+        for (int m = 0; m < Plan<MA>::E; ++m) UA[j * sA + plane_at(t + Plan<MA>::TPS * m, ldA) + l] = v[m];
       });
   __syncthreads();
   // D: inverse rows of UA[j] (1/MA^2) and forward rows of layer b's input -> TB[j] [MA][LB]
@@ -328,15 +204,15 @@ __global__ __launch_bounds__(NT) void k_tail_fwd(SpecLayout in, const float *__r
     for (int r0 = 0; r0 + ln.first < JL * P; r0 += SEQ) {
       const int it = r0 + ln.first + ln.s;
       const bool act = it < JL * P;
-      const int j = act ? it / P : 0, r = 2 * (act ? it % P : 0);
-      const float2 *u = UA + j * MA * ldA + r * ldA;
+      const int j = act ? it / P : 0, r = act ? it % P : 0;
+      const float2 *u = UA + j * sA + plane_at(r, ldA);
       float2 v[Plan<MA>::E];
-      c2r_in<MA, LA>(v, [&](int rr, int k) { return u[rr * ldA + k]; }, ln.t, inv, 1.f);
-      fft_seq<MA, +1, true, true, kLdsPad, Plan<MA>>(v, ln.t, scr, (ln.first + ln.s) * MA, 1, tw, NA / MA);
-      fft_seq<MA, -1, true, true, kLdsPad, Plan<MA>>(v, ln.t, scr, (ln.first + ln.s) * MA, 1, tw, NA / MA);
-      float2 *tb = TB + j * MA * ldB + r * ldB;
-      r2c_out<MA, LB>(v, scr, ln.first + ln.s, ln.t, 1.f, 1.f, [&](int rr, int k, float2 val) {
-        if (act) tb[rr * ldB + k] = val;
+      c2r_in<MA, LA>(v, [&](int rr, int k) { return u[rr * plane_at(MA / 2, ldA) + k]; }, ln.t, inv, 1.f);
+      fft_seq<MA, +1, true, true, kLdsSeq, Plan<MA>>(v, ln.t, scr, (ln.first + ln.s) * row_slot<MA>(), 1, tw, NA / MA);
+      fft_seq<MA, -1, true, true, kLdsSeq, Plan<MA>>(v, ln.t, scr, (ln.first + ln.s) * row_slot<MA>(), 1, tw, NA / MA);
+      float2 *tb = TB + j * sC + plane_at(r, ldC);
+      r2c_out<MA, LB>(v, scr + (ln.first + ln.s) * row_slot<MA>(), ln.t, 1.f, 1.f, [&](int rr, int k, float2 val) {
+        if (act) tb[rr * plane_at(MA / 2, ldC) + k] = val;
       });
     }
   }
@@ -346,9 +222,9 @@ __global__ __launch_bounds__(NT) void k_tail_fwd(SpecLayout in, const float *__r
       JL, LB, tw, NA / MA,
       [&](float2 (&v)[Plan<MA>::E], int j, int l, int t, bool) {
 #pragma unroll
-        for (int m = 0; m < Plan<MA>::E; ++m) v[m] = TB[j * MA * ldB + (t + Plan<MA>::TPS * m) * ldB + l];
+        for (int m = 0; m < Plan<MA>::E; ++m) v[m] = TB[j * sC + plane_at(t + Plan<MA>::TPS * m, ldC) + l];
       },
-      [&](int j) { return TB + j * MA * ldB; },
+      [&](int j) { return TB + j * sC; },
       [&](const float2 (&v)[Plan<MA>::E], int j, int l, int t, bool act) {
         if (!act) return;
         const long long plane = (long long)b * Sa + c * JA + j0 + j;
@@ -357,7 +233,7 @@ __global__ __launch_bounds__(NT) void k_tail_fwd(SpecLayout in, const float *__r
           const int k = t + Plan<MA>::TPS * m;
           if (k < MB / 2 || k >= MA - MB / 2) {
             const int mrow = k < MB / 2 ? k : k - (MA - MB);
-            XB[j * MB * ldB + mrow * ldB + l] = v[m];
+            XB[j * sB + plane_at(mrow, ldB) + l] = v[m];
             *spec_at(saved_b, plane, mrow, l, LB) = v[m];
           }
         }
@@ -372,14 +248,14 @@ __global__ __launch_bounds__(NT) void k_tail_fwd(SpecLayout in, const float *__r
 #pragma unroll
         for (int m = 0; m < Plan<MB>::E; ++m) {
           const int mrow = t + Plan<MB>::TPS * m;
-          v[m] = cmul(XB[j * MB * ldB + mrow * ldB + l], PF ? kpb[m] : kc[(long long)kept<MA, MB>(mrow) * NFB]);
+          v[m] = cmul(XB[j * sB + plane_at(mrow, ldB) + l], PF ? kpb[m] : kc[(long long)kept<MA, MB>(mrow) * NFB]);
         }
       },
-      [&](int q) { return UB + q * MB * ldB; },
+      [&](int q) { return UB + q * sB; },
       [&](const float2 (&v)[Plan<MB>::E], int q, int l, int t, bool act) {
         if (!act) return;
 #pragma unroll
-        for (int m = 0; m < Plan<MB>::E; ++m) UB[q * MB * ldB + (t + Plan<MB>::TPS * m) * ldB + l] = v[m];
+        for (int m = 0; m < Plan<MB>::E; ++m) UB[q * sB + plane_at(t + Plan<MB>::TPS * m, ldB) + l] = v[m];
       });
   __syncthreads();
   // G: inverse rows of UB[q] (1/MB^2) -> y [b][(c JA + j0) JB + q]
@@ -391,17 +267,17 @@ __global__ __launch_bounds__(NT) void k_tail_fwd(SpecLayout in, const float *__r
     for (int r0 = 0; r0 + ln.first < JL * JB * P; r0 += SEQ) {
       const int it = r0 + ln.first + ln.s;
       const bool act = it < JL * JB * P;
-      const int q = act ? it / P : 0, r = 2 * (act ? it % P : 0);
-      const float2 *u = UB + q * MB * ldB + r * ldB;
+      const int q = act ? it / P : 0, r = act ? it % P : 0;
+      const float2 *u = UB + q * sB + plane_at(r, ldB);
       float2 v[Plan<MB>::E];
-      c2r_in<MB, LB>(v, [&](int rr, int k) { return u[rr * ldB + k]; }, ln.t, inv, 1.f);
-      fft_seq<MB, +1, true, true, kLdsPad, Plan<MB>>(v, ln.t, scr, (ln.first + ln.s) * MB, 1, tw, NA / MB);
+      c2r_in<MB, LB>(v, [&](int rr, int k) { return u[rr * plane_at(MB / 2, ldB) + k]; }, ln.t, inv, 1.f);
+      fft_seq<MB, +1, true, true, kLdsSeq, Plan<MB>>(v, ln.t, scr, (ln.first + ln.s) * row_slot<MB>(), 1, tw, NA / MB);
       if (act) {
         float *yr = y + ((long long)b * Sb + (c * JA + j0) * JB + q) * MB * MB + (long long)r * MB;
 #pragma unroll
         for (int m = 0; m < Plan<MB>::E; ++m) {
           yr[ln.t + TPS * m] = v[m].x;
-          yr[MB + ln.t + TPS * m] = v[m].y;
+          yr[MB / 2 * MB + ln.t + TPS * m] = v[m].y;
         }
       }
     }
@@ -425,7 +301,8 @@ __global__ __launch_bounds__(NT) void k_tail_bwd(const float *__restrict__ gy, S
                                                  float2 *__restrict__ part_a, float2 *__restrict__ part_b,
                                                  SpecLayout Tg, float a_out, float *__restrict__ gx, int B, int C) {
   using G = TailGeom<NA, MA, MB, JA, JB>;
-  constexpr int LA = G::LA, LB = G::LB, ldA = G::ldA, ldB = G::ldB;
+  constexpr int LA = G::LA, LB = G::LB, ldT = G::ldT, ldA = G::ldA, ldC = G::ldC, ldB = G::ldB;
+  constexpr int sA = G::sA, sC = G::sC, sB = G::sB;
   constexpr int NFA = NA / 2 + 1, NFB = MA / 2 + 1;
   float2 *tw = t_lds;
   stage_twiddles<NA>(tw, threadIdx.x, NT);
@@ -464,15 +341,15 @@ __global__ __launch_bounds__(NT) void k_tail_bwd(const float *__restrict__ gy, S
     for (int r0 = 0; r0 + ln.first < JA * JB * P; r0 += SEQ) {
       const int it = r0 + ln.first + ln.s;
       const bool act = it < JA * JB * P;
-      const int q = act ? it / P : 0, r = 2 * (act ? it % P : 0);
+      const int q = act ? it / P : 0, r = act ? it % P : 0;
       const float *gr = gy + ((long long)b * Sb + c * JA * JB + q) * MB * MB + (long long)r * MB;
       float2 v[Plan<MB>::E];
 #pragma unroll
-      for (int m = 0; m < Plan<MB>::E; ++m) v[m] = make_float2(gr[ln.t + TPS * m], gr[MB + ln.t + TPS * m]);
-      fft_seq<MB, -1, true, true, kLdsPad, Plan<MB>>(v, ln.t, scr, (ln.first + ln.s) * MB, 1, tw, NA / MB);
-      float2 *g = GB + q * MB * ldB + r * ldB;
-      r2c_out<MB, LB>(v, scr, ln.first + ln.s, ln.t, inv, 2.f, [&](int rr, int k, float2 val) {
-        if (act) g[rr * ldB + k] = val;
+      for (int m = 0; m < Plan<MB>::E; ++m) v[m] = make_float2(gr[ln.t + TPS * m], gr[MB / 2 * MB + ln.t + TPS * m]);
+      fft_seq<MB, -1, true, true, kLdsSeq, Plan<MB>>(v, ln.t, scr, (ln.first + ln.s) * row_slot<MB>(), 1, tw, NA / MB);
+      float2 *g = GB + q * sB + plane_at(r, ldB);
+      r2c_out<MB, LB>(v, scr + (ln.first + ln.s) * row_slot<MB>(), ln.t, inv, 2.f, [&](int rr, int k, float2 val) {
+        if (act) g[rr * plane_at(MB / 2, ldB) + k] = val;
       });
     }
   }
@@ -482,9 +359,9 @@ __global__ __launch_bounds__(NT) void k_tail_bwd(const float *__restrict__ gy, S
       JA * JB, LB, tw, NA / MB,
       [&](float2 (&v)[Plan<MB>::E], int q, int l, int t, bool) {
 #pragma unroll
-        for (int m = 0; m < Plan<MB>::E; ++m) v[m] = GB[q * MB * ldB + (t + Plan<MB>::TPS * m) * ldB + l];
+        for (int m = 0; m < Plan<MB>::E; ++m) v[m] = GB[q * sB + plane_at(t + Plan<MB>::TPS * m, ldB) + l];
       },
-      [&](int q) { return GB + q * MB * ldB; },
+      [&](int q) { return GB + q * sB; },
       [&](const float2 (&v)[Plan<MB>::E], int q, int l, int t, bool act) {
         const int lc = act ? l : 0;
         const int oa = c * JA + q / JB, ob = c * JA * JB + q;
@@ -498,7 +375,7 @@ __global__ __launch_bounds__(NT) void k_tail_bwd(const float *__restrict__ gy, S
           const float2 kv = kc[(long long)kept<MA, MB>(row) * NFB];
           if (act) {
             pp[(long long)row * LB] = cmulc(v[m], xv);
-            GB[q * MB * ldB + row * ldB + l] = cmulc(v[m], kv);
+            GB[q * sB + plane_at(row, ldB) + l] = cmulc(v[m], kv);
           }
         }
       });
@@ -514,16 +391,16 @@ __global__ __launch_bounds__(NT) void k_tail_bwd(const float *__restrict__ gy, S
           if (k < MB / 2 || k >= MA - MB / 2) {
             const int mrow = k < MB / 2 ? k : k - (MA - MB);
 #pragma unroll
-            for (int i = 0; i < JB; ++i) s = cadd(s, GB[(j * JB + i) * MB * ldB + mrow * ldB + l]);
+            for (int i = 0; i < JB; ++i) s = cadd(s, GB[(j * JB + i) * sB + plane_at(mrow, ldB) + l]);
           }
           v[m] = s;
         }
       },
-      [&](int j) { return VB + j * MA * ldB; },
+      [&](int j) { return VB + j * sC; },
       [&](const float2 (&v)[Plan<MA>::E], int j, int l, int t, bool act) {
         if (!act) return;
 #pragma unroll
-        for (int m = 0; m < Plan<MA>::E; ++m) VB[j * MA * ldB + (t + Plan<MA>::TPS * m) * ldB + l] = v[m];
+        for (int m = 0; m < Plan<MA>::E; ++m) VB[j * sC + plane_at(t + Plan<MA>::TPS * m, ldC) + l] = v[m];
       });
   __syncthreads();
   // S4: rfft2-adjoint rows of VB[j] (weights 1, 1/2) and (c_l / MA^2) forward rows -> GA[j] [MA][LA]
@@ -535,15 +412,15 @@ __global__ __launch_bounds__(NT) void k_tail_bwd(const float *__restrict__ gy, S
     for (int r0 = 0; r0 + ln.first < JA * P; r0 += SEQ) {
       const int it = r0 + ln.first + ln.s;
       const bool act = it < JA * P;
-      const int j = act ? it / P : 0, r = 2 * (act ? it % P : 0);
-      const float2 *u = VB + j * MA * ldB + r * ldB;
+      const int j = act ? it / P : 0, r = act ? it % P : 0;
+      const float2 *u = VB + j * sC + plane_at(r, ldC);
       float2 v[Plan<MA>::E];
-      c2r_in<MA, LB>(v, [&](int rr, int k) { return u[rr * ldB + k]; }, ln.t, 1.f, 0.5f);
-      fft_seq<MA, +1, true, true, kLdsPad, Plan<MA>>(v, ln.t, scr, (ln.first + ln.s) * MA, 1, tw, NA / MA);
-      fft_seq<MA, -1, true, true, kLdsPad, Plan<MA>>(v, ln.t, scr, (ln.first + ln.s) * MA, 1, tw, NA / MA);
-      float2 *g = GA + j * MA * ldA + r * ldA;
-      r2c_out<MA, LA>(v, scr, ln.first + ln.s, ln.t, inv, 2.f, [&](int rr, int k, float2 val) {
-        if (act) g[rr * ldA + k] = val;
+      c2r_in<MA, LB>(v, [&](int rr, int k) { return u[rr * plane_at(MA / 2, ldC) + k]; }, ln.t, 1.f, 0.5f);
+      fft_seq<MA, +1, true, true, kLdsSeq, Plan<MA>>(v, ln.t, scr, (ln.first + ln.s) * row_slot<MA>(), 1, tw, NA / MA);
+      fft_seq<MA, -1, true, true, kLdsSeq, Plan<MA>>(v, ln.t, scr, (ln.first + ln.s) * row_slot<MA>(), 1, tw, NA / MA);
+      float2 *g = GA + j * sA + plane_at(r, ldA);
+      r2c_out<MA, LA>(v, scr + (ln.first + ln.s) * row_slot<MA>(), ln.t, inv, 2.f, [&](int rr, int k, float2 val) {
+        if (act) g[rr * plane_at(MA / 2, ldA) + k] = val;
       });
     }
   }
@@ -553,9 +430,9 @@ __global__ __launch_bounds__(NT) void k_tail_bwd(const float *__restrict__ gy, S
       JA, LA, tw, NA / MA,
       [&](float2 (&v)[Plan<MA>::E], int j, int l, int t, bool) {
 #pragma unroll
-        for (int m = 0; m < Plan<MA>::E; ++m) v[m] = GA[j * MA * ldA + (t + Plan<MA>::TPS * m) * ldA + l];
+        for (int m = 0; m < Plan<MA>::E; ++m) v[m] = GA[j * sA + plane_at(t + Plan<MA>::TPS * m, ldA) + l];
       },
-      [&](int j) { return GA + j * MA * ldA; },
+      [&](int j) { return GA + j * sA; },
       [&](const float2 (&v)[Plan<MA>::E], int j, int l, int t, bool act) {
         const int lc = act ? l : 0;
         const int oa = c * JA + j;
@@ -569,7 +446,7 @@ __global__ __launch_bounds__(NT) void k_tail_bwd(const float *__restrict__ gy, S
           const float2 kv = P5 ? kp5[m] : kc[(long long)kept<NA, MA>(row) * NFA];
           if (act) {
             pp[(long long)row * LA] = cmulc(v[m], xv);
-            GA[j * MA * ldA + row * ldA + l] = cmulc(v[m], kv);
+            GA[j * sA + plane_at(row, ldA) + l] = cmulc(v[m], kv);
           }
         }
       });
@@ -586,7 +463,7 @@ __global__ __launch_bounds__(NT) void k_tail_bwd(const float *__restrict__ gy, S
           if (k < MA / 2 || k >= NA - MA / 2) {
             const int mrow = k < MA / 2 ? k : k - (NA - MA);
 #pragma unroll
-            for (int j = 0; j < JA; ++j) s = cadd(s, GA[j * MA * ldA + mrow * ldA + l]);
+            for (int j = 0; j < JA; ++j) s = cadd(s, GA[j * sA + plane_at(mrow, ldA) + l]);
           }
           v[m] = s;
         }
@@ -595,7 +472,7 @@ __global__ __launch_bounds__(NT) void k_tail_bwd(const float *__restrict__ gy, S
       [&](const float2 (&v)[Plan<NA>::E], int, int l, int t, bool act) {
         if (!act) return;
 #pragma unroll
-        for (int m = 0; m < Plan<NA>::E; ++m) VA[(t + Plan<NA>::TPS * m) * ldA + l] = v[m];
+        for (int m = 0; m < Plan<NA>::E; ++m) VA[plane_at(t + Plan<NA>::TPS * m, ldT) + l] = v[m];
       });
   __syncthreads();
   // S7: rfft2-adjoint rows of VA (weights 1, 1/2), then either the previous layer's
@@ -608,24 +485,24 @@ __global__ __launch_bounds__(NT) void k_tail_bwd(const float *__restrict__ gy, S
     for (int r0 = 0; r0 + ln.first < NA / 2; r0 += SEQ) {
       const int p = r0 + ln.first + ln.s;
       const bool act = p < NA / 2;
-      const int r = 2 * (act ? p : 0);
-      const float2 *u = VA + r * ldA;
+      const int r = act ? p : 0;  // rows r and r + N/2
+      const float2 *u = VA + plane_at(r, ldT);
       float2 v[Plan<NA>::E];
-      c2r_in<NA, LA>(v, [&](int rr, int k) { return u[rr * ldA + k]; }, ln.t, 1.f, 0.5f);
-      fft_seq<NA, +1, true, true, kLdsPad, Plan<NA>>(v, ln.t, scr, (ln.first + ln.s) * NA, 1, tw, 1);
+      c2r_in<NA, LA>(v, [&](int rr, int k) { return u[rr * plane_at(NA / 2, ldT) + k]; }, ln.t, 1.f, 0.5f);
+      fft_seq<NA, +1, true, true, kLdsSeq, Plan<NA>>(v, ln.t, scr, (ln.first + ln.s) * row_slot<NA>(), 1, tw, 1);
       if constexpr (OUT == 1) {
         if (act) {
           float *gr = gx + plane * NA * NA + (long long)r * NA;
 #pragma unroll
           for (int m = 0; m < Plan<NA>::E; ++m) {
             gr[ln.t + TPS * m] = v[m].x;
-            gr[NA + ln.t + TPS * m] = v[m].y;
+            gr[NA / 2 * NA + ln.t + TPS * m] = v[m].y;
           }
         }
       } else {
-        fft_seq<NA, -1, true, true, kLdsPad, Plan<NA>>(v, ln.t, scr, (ln.first + ln.s) * NA, 1, tw, 1);
-        r2c_out<NA, NFA>(v, scr, ln.first + ln.s, ln.t, a_out, 2.f, [&](int rr, int k, float2 val) {
-          if (act) *spec_at(Tg, plane, r + rr, k, NFA) = val;
+        fft_seq<NA, -1, true, true, kLdsSeq, Plan<NA>>(v, ln.t, scr, (ln.first + ln.s) * row_slot<NA>(), 1, tw, 1);
+        r2c_out<NA, NFA>(v, scr + (ln.first + ln.s) * row_slot<NA>(), ln.t, a_out, 2.f, [&](int rr, int k, float2 val) {
+          if (act) *spec_at(Tg, plane, r + rr * (NA / 2), k, NFA) = val;
         });
       }
     }
@@ -642,8 +519,8 @@ __global__ __launch_bounds__(NT) void k_tail_bwd(const float *__restrict__ gy, S
 // ----------------------------------------------------------------------------
 template <int N, int P>
 struct Small2d {
-  static constexpr int L = N / 2 + 1, ld = plane_ld(L), NT = 256;
-  static constexpr int TW = twiddle_lds_elems<N>(), PL = TW, SCR = PL + P * N * ld;
+  static constexpr int L = N / 2 + 1, ld = plane_ld<N>(L), SZ = plane_size(N, ld), NT = 256;
+  static constexpr int TW = twiddle_lds_elems<N>(), PL = TW, SCR = PL + P * SZ;
   static constexpr int END = SCR + row_scratch<N, NT>(P * N / 2);
 };
 
@@ -651,7 +528,7 @@ template <int N, int P>
 __global__ __launch_bounds__(256) void k_fft2_small_fwd(const float *__restrict__ x, float2 *__restrict__ X,
                                                         long long count, float a2, float b2) {
   using G = Small2d<N, P>;
-  constexpr int L = G::L, ld = G::ld, NT = G::NT, TPS = Plan<N>::TPS, E = Plan<N>::E;
+  constexpr int L = G::L, ld = G::ld, SZ = G::SZ, NT = G::NT, TPS = Plan<N>::TPS, E = Plan<N>::E;
   float2 *tw = t_lds, *pl = t_lds + G::PL, *scr = t_lds + G::SCR;
   stage_twiddles<N>(tw, threadIdx.x, NT);
   const long long q0 = (long long)xcd_remap(blockIdx.x, gridDim.x) * P;
@@ -662,15 +539,15 @@ __global__ __launch_bounds__(256) void k_fft2_small_fwd(const float *__restrict_
     for (int r0 = 0; r0 + ln.first < np * H; r0 += SEQ) {
       const int it = r0 + ln.first + ln.s;
       const bool act = it < np * H;
-      const int q = act ? it / H : 0, r = 2 * (act ? it % H : 0);
+      const int q = act ? it / H : 0, r = act ? it % H : 0;
       const float *xr = x + ((q0 + q) * N + r) * N;
       float2 v[E];
 #pragma unroll
-      for (int m = 0; m < E; ++m) v[m] = make_float2(xr[ln.t + TPS * m], xr[N + ln.t + TPS * m]);
-      fft_seq<N, -1, true, true, kLdsPad, Plan<N>>(v, ln.t, scr, (ln.first + ln.s) * N, 1, tw, 1);
-      float2 *dst = pl + (q * N + r) * ld;
-      r2c_out<N, L>(v, scr, ln.first + ln.s, ln.t, a2, b2, [&](int rr, int k, float2 val) {
-        if (act) dst[rr * ld + k] = val;
+      for (int m = 0; m < E; ++m) v[m] = make_float2(xr[ln.t + TPS * m], xr[N / 2 * N + ln.t + TPS * m]);
+      fft_seq<N, -1, true, true, kLdsSeq, Plan<N>>(v, ln.t, scr, (ln.first + ln.s) * row_slot<N>(), 1, tw, 1);
+      float2 *dst = pl + q * SZ + plane_at(r, ld);
+      r2c_out<N, L>(v, scr + (ln.first + ln.s) * row_slot<N>(), ln.t, a2, b2, [&](int rr, int k, float2 val) {
+        if (act) dst[rr * plane_at(N / 2, ld) + k] = val;
       });
     }
   }
@@ -679,9 +556,9 @@ __global__ __launch_bounds__(256) void k_fft2_small_fwd(const float *__restrict_
       np, L, tw, 1,
       [&](float2 (&v)[E], int q, int l, int t, bool) {
 #pragma unroll
-        for (int m = 0; m < E; ++m) v[m] = pl[(q * N + t + TPS * m) * ld + l];
+        for (int m = 0; m < E; ++m) v[m] = pl[q * SZ + plane_at(t + TPS * m, ld) + l];
       },
-      [&](int q) { return pl + q * N * ld; },
+      [&](int q) { return pl + q * SZ; },
       [&](const float2 (&v)[E], int q, int l, int t, bool act) {
         if (!act) return;
         float2 *o = X + (q0 + q) * N * L + l;
@@ -694,7 +571,7 @@ template <int N, int P>
 __global__ __launch_bounds__(256) void k_fft2_small_inv(const float2 *__restrict__ X, float *__restrict__ x,
                                                         long long count, float a1, float b1) {
   using G = Small2d<N, P>;
-  constexpr int L = G::L, ld = G::ld, NT = G::NT, TPS = Plan<N>::TPS, E = Plan<N>::E;
+  constexpr int L = G::L, ld = G::ld, SZ = G::SZ, NT = G::NT, TPS = Plan<N>::TPS, E = Plan<N>::E;
   float2 *tw = t_lds, *pl = t_lds + G::PL, *scr = t_lds + G::SCR;
   stage_twiddles<N>(tw, threadIdx.x, NT);
   const long long q0 = (long long)xcd_remap(blockIdx.x, gridDim.x) * P;
@@ -706,11 +583,11 @@ __global__ __launch_bounds__(256) void k_fft2_small_inv(const float2 *__restrict
 #pragma unroll
         for (int m = 0; m < E; ++m) v[m] = c[(t + TPS * m) * L];
       },
-      [&](int q) { return pl + q * N * ld; },
+      [&](int q) { return pl + q * SZ; },
       [&](const float2 (&v)[E], int q, int l, int t, bool act) {
         if (!act) return;
 #pragma unroll
-        for (int m = 0; m < E; ++m) pl[(q * N + t + TPS * m) * ld + l] = v[m];
+        for (int m = 0; m < E; ++m) pl[q * SZ + plane_at(t + TPS * m, ld) + l] = v[m];
       });
   __syncthreads();
   {  // rows: inverse of pairs of rows packed as one complex sequence -> real rows
@@ -719,15 +596,15 @@ __global__ __launch_bounds__(256) void k_fft2_small_inv(const float2 *__restrict
     for (int r0 = 0; r0 + ln.first < np * H; r0 += SEQ) {
       const int it = r0 + ln.first + ln.s;
       const bool act = it < np * H;
-      const int q = act ? it / H : 0, r = 2 * (act ? it % H : 0);
-      const float2 *src = pl + (q * N + r) * ld;
+      const int q = act ? it / H : 0, r = act ? it % H : 0;
+      const float2 *src = pl + q * SZ + plane_at(r, ld);
       float2 v[E];
-      c2r_in<N, L>(v, [&](int rr, int k) { return src[rr * ld + k]; }, ln.t, a1, b1);
-      fft_seq<N, +1, true, true, kLdsPad, Plan<N>>(v, ln.t, scr, (ln.first + ln.s) * N, 1, tw, 1);
+      c2r_in<N, L>(v, [&](int rr, int k) { return src[rr * plane_at(N / 2, ld) + k]; }, ln.t, a1, b1);
+      fft_seq<N, +1, true, true, kLdsSeq, Plan<N>>(v, ln.t, scr, (ln.first + ln.s) * row_slot<N>(), 1, tw, 1);
       if (act) {
         float *xr = x + ((q0 + q) * N + r) * N;
 #pragma unroll
-        for (int m = 0; m < E; ++m) xr[ln.t + TPS * m] = v[m].x, xr[N + ln.t + TPS * m] = v[m].y;
+        for (int m = 0; m < E; ++m) xr[ln.t + TPS * m] = v[m].x, xr[N / 2 * N + ln.t + TPS * m] = v[m].y;
       }
     }
   }
@@ -781,14 +658,6 @@ static bool dispatch_tail(int na, int ma, int mb, int ja, int jb, F &&f) {
 
 bool tail_supported(int na, int ma, int mb, int ja, int jb) {
   return dispatch_tail(na, ma, mb, ja, jb, [](auto, auto, auto, auto, auto) {});
-}
-
-// Raise a kernel's dynamic LDS limit to `bytes` (once per kernel).
-template <auto Kern>
-static hipError_t allow_lds(size_t bytes) {
-  static const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(Kern),
-                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-  return e;
 }
 
 template <auto Kern, class... Args>
