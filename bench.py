@@ -295,8 +295,8 @@ def spatial_step_launches(wl, n, input_grad=False, ranges=None):
         if gx:
             out.append((f"col_bwd_gx_{N}_{M}", C64 * (B * S * M * L + S * M * L + B * C * N * L)))
             out.append((f"row_c2r_{N}", C64 * B * C * N * L + F32 * B * C * N * N))
-        out.append(("cic_wgrad", C64 * S * M * L))
-        out.append(("cic_wgrad_reduce", F32 * S * n * n))
+        out.append(("cic_wgrad_stack", C64 * S * M * L))
+        out.append(("cic_wgrad_stack_reduce", F32 * S * n * n))
     return out
 
 
@@ -608,8 +608,8 @@ def full_cic_step_launches(wl, ranges=1):
         *gk_launches(B, C, S, P, P, L, L, ranges),
         (f"col_bwd_gx_{P}_{P}", C64 * (B * S * P * L + S * P * L + B * C * P * L)),
         (f"row_c2r_{P}", C64 * B * C * P * L + F32 * B * C * P * P),
-        ("cic_wgrad", C64 * S * P * L),
-        ("cic_wgrad_reduce", F32 * S * n * n),
+        ("cic_wgrad_stack", C64 * S * P * L),
+        ("cic_wgrad_stack_reduce", F32 * S * n * n),
     ]
 
 

@@ -621,7 +621,7 @@ SpatialWs spatial_layout(const fdc_layer_plan *p) {
   w.fwd = kbytes + align256(p->fwd_ws);
   w.gk = kbytes;
   w.part = w.gk + kbytes;
-  w.layer = w.part + align256((size_t)p->S * fdc::cic_wgrad_blocks(p->M) * p->ksz * p->ksz * sizeof(float));
+  w.layer = w.part + align256((size_t)p->S * fdc::cic_wgrad_stack_blocks(p->M) * p->ksz * p->ksz * sizeof(float));
   w.bwd = w.layer + align256(p->bwd_ws);
   return w;
 }

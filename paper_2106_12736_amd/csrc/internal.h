@@ -228,12 +228,11 @@ hipError_t launch_cic_bwd_gx(const float2 *gY, const float2 *K, float2 *gX, int 
 hipError_t launch_cic_bwd_gk(const float2 *gY, const float2 *X, float2 *gK, int B, int C, int S, long long P,
                              hipStream_t s);
 // Spatial-kernel CIC: kernel spectra of n x n kernels at the kept bins of an n_img -> M
-// layer (into K [S][n_img][n_img/2+1]), and dL/dw from dK (part: S * cic_wgrad_blocks(M)
-// * n * n floats of scratch).
+// layer (into K [S][n_img][n_img/2+1]), and dL/dw from dK (part: S *
+// cic_wgrad_stack_blocks(M) * n * n floats of scratch).
 bool spatial_kernel_size_supported(int n);
 // Output channels the spatial-kernel weight-gradient launch accepts.
 bool spatial_channels_supported(int S);
-int cic_wgrad_blocks(int M);
 // One layer of a batched spatial-kernel call (k_cic_kspec_stack, k_cic_wgrad_stack):
 // the caller fills w, K (kspec) or gK, part, gw (wgrad), N, M, S, n and roll (the ROLL
 // shift s, 0 for none); the launchers fill the grid fields.

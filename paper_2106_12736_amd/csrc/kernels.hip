@@ -2177,86 +2177,6 @@ __global__ __launch_bounds__(256) void k_cic_kspec(const float *__restrict__ w, 
   }
 }
 
-// dL/dw of those kernels from dK [S][N][N/2+1] at the kept bins (the rfft2 adjoint
-// restricted to the n x n support): dL/dw[o][a][b] = Re sum dK(k, l) conj(W^(k a + l b)).
-// Workgroup (rb, o) takes rows rb, rb + RB, ... of the M kept rows; a wave sums one
-// row at a time, E_b = sum_l dK(k, l) conj(W^(l b)) reduced across its lanes, and
-// adds Re(E_b conj(W^(k a))).  Partial sums part [S][RB][n n] are added in order by
-// k_cic_wgrad_reduce.  n <= kSpatialMaxN.
-template <int N>
-__global__ __launch_bounds__(256) void k_cic_wgrad_part(const float2 *__restrict__ gK, float *__restrict__ part,
-                                                        int n, int M, int RB) {
-  constexpr int NF = N / 2 + 1;
-  __shared__ float2 tw[N];
-  for (int i = threadIdx.x; i < N; i += 256) tw[i] = twiddle_load<N>(i);
-  __syncthreads();
-  const int L = M / 2 + 1;
-  const int rb = blockIdx.x, o = blockIdx.y;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  float acc[kSpatialMaxN * kSpatialMaxN];
-#pragma unroll
-  for (int i = 0; i < kSpatialMaxN * kSpatialMaxN; ++i) acc[i] = 0.f;
-  for (int k = rb + RB * wave; k < M; k += 4 * RB) {
-    const int kr = k < M / 2 ? k : k + (N - M);
-    const float2 *row = gK + ((long long)o * N + kr) * NF;
-    float ex[kSpatialMaxN], ey[kSpatialMaxN];
-#pragma unroll
-    for (int b = 0; b < kSpatialMaxN; ++b) ex[b] = ey[b] = 0.f;
-    for (int l = lane; l < L; l += 64) {
-      const float2 g = row[l];
-#pragma unroll
-      for (int b = 0; b < kSpatialMaxN; ++b) {
-        if (b < n) {
-          const float2 v = tw[(l * b) % N];  // g conj(v)
-          ex[b] = fmaf(g.x, v.x, fmaf(g.y, v.y, ex[b]));
-          ey[b] = fmaf(g.y, v.x, fmaf(-g.x, v.y, ey[b]));
-        }
-      }
-    }
-#pragma unroll
-    for (int b = 0; b < kSpatialMaxN; ++b) {
-      if (b < n) {
-        for (int off = 32; off > 0; off >>= 1) {
-          ex[b] += __shfl_xor(ex[b], off);
-          ey[b] += __shfl_xor(ey[b], off);
-        }
-      }
-    }
-#pragma unroll
-    for (int a = 0; a < kSpatialMaxN; ++a) {
-      if (a < n) {
-        const float2 u = tw[(kr * a) % N];
-#pragma unroll
-        for (int b = 0; b < kSpatialMaxN; ++b)
-          if (b < n) acc[a * kSpatialMaxN + b] = fmaf(ex[b], u.x, fmaf(ey[b], u.y, acc[a * kSpatialMaxN + b]));
-      }
-    }
-  }
-  // every lane of a wave holds the wave's sums; add the four waves in order
-  __shared__ float red[4][kSpatialMaxN * kSpatialMaxN];
-  if (lane == 0) {
-#pragma unroll
-    for (int i = 0; i < kSpatialMaxN * kSpatialMaxN; ++i) red[wave][i] = acc[i];
-  }
-  __syncthreads();
-  const int t = threadIdx.x;
-  if (t < n * n) {
-    const int a = t / n, b = t - (t / n) * n;
-    const int i = a * kSpatialMaxN + b;
-    part[((long long)o * RB + rb) * n * n + t] = (red[0][i] + red[1][i]) + (red[2][i] + red[3][i]);
-  }
-}
-
-__global__ void k_cic_wgrad_reduce(const float *__restrict__ part, float *__restrict__ gw, int nn, int RB,
-                                   int total) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= total) return;
-  const int o = i / nn, t = i - (i / nn) * nn;
-  float acc = 0.f;
-  for (int rb = 0; rb < RB; ++rb) acc += part[((long long)o * RB + rb) * nn + t];
-  gw[i] = acc;
-}
-
 // ---------------------------------------------------------------------------
 // The same two steps for every layer of a stack in one launch each (the spatial-kernel
 // stack): layer sizes are runtime values, each workgroup stages its layer's twiddle
@@ -2520,8 +2440,6 @@ bool spatial_channels_supported(int S) { return S >= 1 && S <= 65535; }
 
 bool cic_fdp_size_supported(int N) { return (long long)N * (N / 2 + 1) < (1 << 24); }
 
-int cic_wgrad_blocks(int M) { return M >= 256 ? 32 : (M >= 64 ? 16 : 4); }
-
 hipError_t launch_cic_kspec(int n_img, const float *w, float2 *K, int S, int n, int M, hipStream_t s) {
   if (!spatial_kernel_size_supported(n)) return hipErrorInvalidValue;
   hipError_t err = hipErrorInvalidValue;
@@ -2536,20 +2454,18 @@ hipError_t launch_cic_kspec(int n_img, const float *w, float2 *K, int S, int n, 
   return err;
 }
 
+// One layer's weight gradient is the stack's launch with one layer: a lane sums a column of
+// dK down the rows and the workgroup projects its 64 columns once, instead of a cross-lane
+// reduction for every row (512 channels of 64 x 64, 3 x 3 taps: 39 -> 9 us with the sum of
+// the partials).
 hipError_t launch_cic_wgrad(int n_img, const float2 *gK, float *part, float *gw, int S, int n, int M,
                             hipStream_t s) {
-  if (!spatial_kernel_size_supported(n)) return hipErrorInvalidValue;
-  const int RB = cic_wgrad_blocks(M);
-  hipError_t err = hipErrorInvalidValue;
-  dispatch_n(n_img, [&](auto nc) {
-    constexpr int N = decltype(nc)::value;
-    if (S > 65535) return;
-    err = timed_launch("cic_wgrad", k_cic_wgrad_part<N>, dim3(RB, S), dim3(256), 0, s, gK, part, n, M, RB);
-  });
-  if (err != hipSuccess) return err;
-  const int total = S * n * n;
-  return launch("cic_wgrad_reduce", k_cic_wgrad_reduce, (unsigned)((total + 255) / 256), 256, 0, s, part, gw, n * n,
-                RB, total);
+  if (!spatial_kernel_size_supported(n) || S > 65535) return hipErrorInvalidValue;
+  SpatialBatch sb{};
+  sb.count = 1;
+  sb.layer[0].gK = gK, sb.layer[0].part = part, sb.layer[0].gw = gw;
+  sb.layer[0].N = n_img, sb.layer[0].M = M, sb.layer[0].S = S, sb.layer[0].n = n;
+  return launch_cic_wgrad_stack(sb, s);
 }
 
 hipError_t launch_cic_fwd(const float2 *X, const float2 *K, float2 *Y, int B, int C, int S, long long P,
