@@ -80,6 +80,45 @@ def gk_launches(B, C, S, N, M, L, NF, ranges=1, zeros=True):
             ("gk_reduce", C64 * (R * S * M * L + gk_bytes))]
 
 
+def small_layer(N, M):
+    """Whether a layer call runs its forward (and most backwards) in one launch."""
+    return (N, M) in ((32, 32), (32, 16), (32, 8), (64, 64), (64, 32), (64, 16), (128, 64), (128, 32))
+
+
+def small_backward(B, C, S, N, M):
+    """The rule of small_bwd_supported (csrc/small.hip)."""
+    J, planes = S // C, B * C
+    if not small_layer(N, M):
+        return False
+    if M == 64:
+        return J == 1 or (J == 2 and (N == 64 or planes < 512)) or (J <= 4 and N == 64 and planes < 512)
+    return not (M == 32 and N <= 64 and J >= 4 and planes >= 1024)
+
+
+def layer_fwd_launches(B, C, S, N, M, L, out):
+    """A layer call's forward from images B x C x N x N to B x S x out x out."""
+    x, y = F32 * B * C * N * N, F32 * B * S * out * out
+    if small_layer(N, M):
+        return [(f"small_fwd_{N}_{M}", x + C64 * (S * M * L + B * C * M * L) + y)]
+    return [(f"row_r2c_{N}", x + C64 * B * C * N * L), *fwd_col_launches(B, C, S, N, M, L),
+            (f"row_c2r_{M}", C64 * B * S * M * L + y)]
+
+
+def layer_bwd_launches(B, C, S, N, M, L, NF, out, ranges=1, dx=True):
+    """A layer call's backward: gK, and gx with dx."""
+    gy, gx = F32 * B * S * out * out, F32 * B * C * N * N
+    if small_backward(B, C, S, N, M):
+        R = ranges
+        gk = R * S * M * L if R > 1 else S * N * NF
+        one = (f"small_bwd_{N}_{M}", gy + C64 * (B * C * M * L + gk) + (C64 * S * M * L + gx if dx else 0))
+        return [one] + ([("gk_reduce", C64 * (R * S * M * L + S * N * NF))] if R > 1 else [])
+    res = [(f"row_r2c_{M}", gy + C64 * B * S * M * L), *gk_launches(B, C, S, N, M, L, NF, ranges)]
+    if dx:
+        res.append((f"col_bwd_gx_{N}_{M}", C64 * (B * S * M * L + S * M * L + B * C * N * L)))
+        res.append((f"row_c2r_{N}", C64 * B * C * N * L + gx))
+    return res
+
+
 def step_launches(wl, input_grad=False, ranges=None):
     """(kernel name, algorithmic bytes) of every launch of one step, in launch order;
     ranges[i]: dK batch ranges of layer i (fdc_cic_layer_dk_ranges, default 1)."""
@@ -87,16 +126,10 @@ def step_launches(wl, input_grad=False, ranges=None):
     out = []
     for i in range(wl.layers):
         B, C, S, N, M, L, _ = layer_dims(wl, i)
-        out.append((f"row_r2c_{N}", F32 * B * C * N * N + C64 * B * C * N * L))
-        out += fwd_col_launches(B, C, S, N, M, L)
-        out.append((f"row_c2r_{M}", C64 * B * S * M * L + F32 * B * S * M * M))
+        out += layer_fwd_launches(B, C, S, N, M, L, M)
     for i in reversed(range(wl.layers)):
         B, C, S, N, M, L, NF = layer_dims(wl, i)
-        out.append((f"row_r2c_{M}", F32 * B * S * M * M + C64 * B * S * M * L))
-        out += gk_launches(B, C, S, N, M, L, NF, ranges[i])
-        if i > 0 or input_grad:
-            out.append((f"col_bwd_gx_{N}_{M}", C64 * (B * S * M * L + S * M * L + B * C * N * L)))
-            out.append((f"row_c2r_{N}", C64 * B * C * N * L + F32 * B * C * N * N))
+        out += layer_bwd_launches(B, C, S, N, M, L, NF, M, ranges[i], i > 0 or input_grad)
     return out
 
 
@@ -282,19 +315,13 @@ def spatial_step_launches(wl, n, input_grad=False, ranges=None):
     for i in range(wl.layers):
         B, C, S, N, M, L, _ = layer_dims(wl, i)
         out.append(("cic_kspec", F32 * S * n * n + C64 * S * M * L))
-        out.append((f"row_r2c_{N}", F32 * B * C * N * N + C64 * B * C * N * L))
-        out += fwd_col_launches(B, C, S, N, M, L)
-        out.append((f"row_c2r_{M}", C64 * B * S * M * L + F32 * B * S * M * M))
+        out += layer_fwd_launches(B, C, S, N, M, L, M)
     for i in reversed(range(wl.layers)):
         B, C, S, N, M, L, NF = layer_dims(wl, i)
         gx = i > 0 or input_grad
         if gx:
             out.append(("cic_kspec", F32 * S * n * n + C64 * S * M * L))
-        out.append((f"row_r2c_{M}", F32 * B * S * M * M + C64 * B * S * M * L))
-        out += gk_launches(B, C, S, N, M, L, NF, ranges[i])
-        if gx:
-            out.append((f"col_bwd_gx_{N}_{M}", C64 * (B * S * M * L + S * M * L + B * C * N * L)))
-            out.append((f"row_c2r_{N}", C64 * B * C * N * L + F32 * B * C * N * N))
+        out += layer_bwd_launches(B, C, S, N, M, L, NF, M, ranges[i], gx)
         out.append(("cic_wgrad_stack", C64 * S * M * L))
         out.append(("cic_wgrad_stack_reduce", F32 * S * n * n))
     return out
@@ -600,14 +627,9 @@ def full_cic_step_launches(wl, ranges=1):
     O = P - n + 1
     return [
         ("cic_kspec", F32 * S * n * n + C64 * S * P * L),
-        (f"row_r2c_{P}", F32 * B * C * P * P + C64 * B * C * P * L),
-        *fwd_col_launches(B, C, S, P, P, L),
-        (f"row_c2r_{P}", C64 * B * S * P * L + F32 * B * S * O * O),
+        *layer_fwd_launches(B, C, S, P, P, L, O),
         ("cic_kspec", F32 * S * n * n + C64 * S * P * L),
-        (f"row_r2c_{P}", F32 * B * S * O * O + C64 * B * S * P * L),
-        *gk_launches(B, C, S, P, P, L, L, ranges),
-        (f"col_bwd_gx_{P}_{P}", C64 * (B * S * P * L + S * P * L + B * C * P * L)),
-        (f"row_c2r_{P}", C64 * B * C * P * L + F32 * B * C * P * P),
+        *layer_bwd_launches(B, C, S, P, P, L, L, O, ranges),
         ("cic_wgrad_stack", C64 * S * P * L),
         ("cic_wgrad_stack_reduce", F32 * S * n * n),
     ]

@@ -427,8 +427,10 @@ fdc_status fdc_kernel_timing_launches(char *buf, size_t buf_bytes);
  * backward workspace (R [S][M][M/2+1] arrays), and a second launch ("gk_reduce")
  * adds the ranges in range order and writes gK, so results stay repeatable.  R
  * depends only on the plan: larger batches are cut into ranges so that enough
- * workgroups run at once.  Layer plans of the spectral-kernel CIC layer (the
- * plan's layer for the stack call); FDC_EINVAL for other plans or layers. */
+ * workgroups run at once.  A layer plan whose whole backward is one launch
+ * ("small_bwd_<N>_<M>", N <= 128) sums R ranges in it and adds them the same way.
+ * Layer plans of the spectral-kernel CIC layer (the plan's layer for the stack call);
+ * FDC_EINVAL for other plans or layers. */
 fdc_status fdc_cic_layer_dk_ranges(const fdc_layer_plan *plan, int *ranges);
 fdc_status fdc_cic_stack_dk_ranges(const fdc_stack_plan *plan, int layer, int *ranges);
 /* The first layer of the stack's LDS-resident tail (the last two layers run by

@@ -551,6 +551,15 @@ fdc_status fdc_cic_layer_forward(const fdc_layer_plan *p, const float *x, const 
   if (!x || !K || !y) return fail(FDC_EINVAL, "NULL tensor");
   if (fdc_status st = check_ws(ws, ws_bytes, p->fwd_ws)) return st;
   const int B = p->B, C = p->C, S = p->S, N = p->N, M = p->M, L = M / 2 + 1;
+  if (fdc::small_layer_supported(N, M)) {
+    const fdc::SpecLayout none{};
+    return check_hip(fdc::launch_small_fwd(N, M, x, reinterpret_cast<const float2 *>(K),
+                                           saved ? fdc::tiled_layout(static_cast<const float2 *>(saved),
+                                                                     (long long)B * C, M, L)
+                                                 : none,
+                                           y, artifact_view(p), (long long)p->out * p->out, B, C, S, s),
+                     "layer forward");
+  }
   auto *T = reinterpret_cast<float2 *>(ws);
   auto *U = T + (size_t)B * C * N * L;
   // the pooled input spectrum goes to `saved` when the caller keeps it, else to the workspace
@@ -579,6 +588,13 @@ fdc_status fdc_cic_layer_backward(const fdc_layer_plan *p, const float *gy, cons
   if (!gx && !gK) return FDC_OK;
   if (fdc_status st = check_ws(ws, ws_bytes, p->bwd_ws)) return st;
   const int B = p->B, C = p->C, S = p->S, N = p->N, M = p->M, L = M / 2 + 1;
+  if (fdc::small_bwd_supported(N, M, B, C, S))  // dK's range sums (at most one per image) take Tg's place
+    return check_hip(fdc::launch_small_bwd(N, M, gy, artifact_view(p), (long long)p->out * p->out,
+                                           fdc::tiled_layout(static_cast<const float2 *>(saved), (long long)B * C, M,
+                                                             L),
+                                           reinterpret_cast<const float2 *>(K), gx, reinterpret_cast<float2 *>(gK),
+                                           static_cast<float2 *>(ws), B, C, S, s),
+                     "layer backward");
   auto *Tg = reinterpret_cast<float2 *>(ws);
   auto *V = Tg + (size_t)B * S * M * L;
   if (fdc_status st = check_hip(fdc::launch_row_r2c(M, gy, fdc::tiled_layout(Tg, (long long)B * S, M, L),
@@ -1261,6 +1277,10 @@ fdc_status fdc_kernel_timing_report(char *buf, size_t buf_bytes) {
 fdc_status fdc_cic_layer_dk_ranges(const fdc_layer_plan *p, int *ranges) {
   if (fdc_status st = check_layer_plan(p, 0)) return st;
   if (ranges == nullptr) return fail(FDC_EINVAL, "ranges is NULL");
+  if (fdc::small_bwd_supported(p->N, p->M, p->B, p->C, p->S)) {
+    *ranges = fdc::small_bwd_ranges(p->M, p->B, p->C, p->S);
+    return FDC_OK;
+  }
   // the same scratch as fdc_cic_layer_backward: the dX buffer
   *ranges = fdc::gk_batch_ranges(p->N, p->M, p->B, p->S, (long long)p->B * p->C * p->N * (p->M / 2 + 1));
   return FDC_OK;

@@ -80,6 +80,61 @@ def test_layer_forward_backward(N, M, B, C, J, artifact, kn):
     assert np.all(to_np(gK)[:, ~kept] == 0)
 
 
+# One-launch layers: every size pair; one image (no partial sums) and several; 1, 2, 4, 8 and
+# 5 output channels a channel (the channels-side-by-side forms and the one-by-one form); crop
+# and roll; enough planes to leave the small-launch forms.
+SMALL_CASES = [
+    # N, M, B, C, J, artifact, kernel_n
+    (32, 32, 1, 3, 5, "crop", 7),
+    (32, 32, 3, 2, 4, "roll", 5),
+    (32, 16, 1, 1, 8, "none", 1),
+    (32, 16, 5, 130, 1, "crop", 3),
+    (32, 8, 2, 3, 2, "roll", 8),
+    (32, 8, 3, 1, 4, "crop", 2),
+    (64, 64, 3, 1, 4, "roll", 3),
+    (64, 64, 1, 2, 1, "crop", 64),
+    (64, 32, 3, 3, 8, "crop", 3),
+    (64, 32, 2, 270, 2, "none", 1),
+    (64, 16, 2, 2, 5, "none", 1),
+    (128, 64, 2, 1, 2, "crop", 5),
+    (128, 64, 3, 2, 1, "roll", 6),
+    (128, 32, 1, 2, 4, "crop", 3),
+    (128, 32, 3, 1, 3, "none", 1),
+]
+
+
+@pytest.mark.parametrize("N,M,B,C,J,artifact,kn", SMALL_CASES)
+def test_small_layer(N, M, B, C, J, artifact, kn):
+    """The one-launch forward and backward, each output also on its own.  Four transforms of
+    log2(N) <= 7 roundings each and sums of at most 8 terms, in units of u = 6e-8 and adding
+    as a random walk, stay below 12 u = 7e-7; the bound is four times that."""
+    print(f"small layer N={N} M={M} B={B} C={C} J={J} {artifact}/{kn}", flush=True)
+    rng = _rng("small", N, M, B, C, J, artifact, kn)
+    S = C * J
+    x = rng.random((B, C, N, N), dtype=np.float32)
+    K = inputs.spectral_kernels(rng, S, N)
+    layer = layers.CicLayer(B, C, S, N, M, artifact, kn)
+    gy = rng.standard_normal((B, S, layer.out, layer.out), dtype=np.float32)
+    xg, Kg, gyg = _gpu(x), _gpu(K), _gpu(gy)
+    saved = layer.new_saved()
+    y = layer.forward(xg, Kg, saved=saved)
+    gx, gK = layer.backward(gyg, saved, Kg)
+    assert torch.equal(y, layer.forward(xg, Kg))
+    only_x, _ = layer.backward(gyg, None, Kg, need_gk=False)
+    _, only_k = layer.backward(gyg, saved, None, need_gx=False)
+    assert torch.equal(gx, only_x) and torch.equal(gK, only_k)
+
+    mode = ORACLE_MODE[artifact]
+    ry, xs = fdc.cic_fdp_layer_forward(x.astype(np.float64), K.astype(np.complex128), M, mode, kn)
+    rgx, rgK = fdc.cic_fdp_layer_backward(gy.astype(np.float64), xs, K.astype(np.complex128), M, mode, kn)
+    for got, ref, name in ((y, ry, "y"), (gx, rgx, "gx"), (gK, rgK, "gK")):
+        assert_parity(to_np(got), ref, name, rel=3e-6)
+    assert_parity(to_np(layer.saved_spectrum(saved)), fdc.fdp(xs, M, M), "saved spectrum", rel=3e-6)
+    kept = np.zeros((N, N // 2 + 1), bool)
+    kept[list(range(M // 2)) + list(range(N - M // 2, N)), : M // 2 + 1] = True
+    assert np.all(to_np(gK)[:, ~kept] == 0)
+
+
 def test_layer_is_deterministic_and_reentrant():
     N, M, B, C, J = 256, 128, 4, 2, 2
     rng = _rng("det")
