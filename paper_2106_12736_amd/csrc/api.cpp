@@ -336,6 +336,11 @@ fdc_status fdc_cic_backward(const fdc_c64 *gY, const fdc_c64 *X, const fdc_c64 *
   if (fdc_status st = check_cic_dims(B, C, S, H, Wf)) return st;
   if (!gY || (gX && !K) || (gK && !X)) return fail(FDC_EINVAL, "NULL tensor");
   const long long P = (long long)H * Wf;
+  if (gX && gK && fdc::cic_bwd_fused(B, C, S, P))
+    return check_hip(fdc::launch_cic_bwd(reinterpret_cast<const float2 *>(gY), reinterpret_cast<const float2 *>(X),
+                                         reinterpret_cast<const float2 *>(K), reinterpret_cast<float2 *>(gX),
+                                         reinterpret_cast<float2 *>(gK), B, C, S, P, s),
+                     "cic_backward");
   if (gX) {
     if (fdc_status st = check_hip(fdc::launch_cic_bwd_gx(reinterpret_cast<const float2 *>(gY),
                                                          reinterpret_cast<const float2 *>(K),

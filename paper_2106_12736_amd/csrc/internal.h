@@ -239,6 +239,10 @@ hipError_t launch_cic_bwd_gx(const float2 *gY, const float2 *K, float2 *gX, int 
                              hipStream_t s);
 hipError_t launch_cic_bwd_gk(const float2 *gY, const float2 *X, float2 *gK, int B, int C, int S, long long P,
                              hipStream_t s);
+// Both gradients in one launch, for the shapes cic_bwd_fused accepts.
+bool cic_bwd_fused(int B, int C, int S, long long P);
+hipError_t launch_cic_bwd(const float2 *gY, const float2 *X, const float2 *K, float2 *gX, float2 *gK, int B, int C,
+                          int S, long long P, hipStream_t s);
 // Spatial-kernel CIC: kernel spectra of n x n kernels at the kept bins of an n_img -> M
 // layer (into K [S][n_img][n_img/2+1]), and dL/dw from dK (part: S *
 // cic_wgrad_stack_blocks(M) * n * n floats of scratch).

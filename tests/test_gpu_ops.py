@@ -162,3 +162,49 @@ def test_fdp(count, H, W, Mh, Mw):
     gY = _crand(rng, (count, Mh, Mw // 2 + 1))
     gX = layers.fdp_backward(_gpu(gY), H, W)
     np.testing.assert_array_equal(to_np(gX), fdc.fdp_backward(gY.astype(np.complex128), H, W).astype(np.complex64))
+
+
+@pytest.mark.parametrize("B,C,S,H,Wf", [
+    (5, 1, 1, 1, 1), (5, 2, 2, 5, 3), (3, 2, 6, 4, 3), (9, 1, 4, 62, 33), (6, 3, 24, 6, 7),
+    (2, 1, 2, 62, 33), (4, 3, 12, 63, 33), (5, 1, 2, 512, 257), (5, 1, 4, 363, 363)])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_cic_spectral_forms(B, C, S, H, Wf, offset):
+    """Bins by twos and one by one (odd planes, tensors off 16 bytes), 1 to 8 output channels a
+    channel, both gradients fused and each on its own.  A product of two complex values and sums
+    of at most 9 of them in float32: at most (2 + 9) roundings of 6e-8, below 7e-7 of the result's
+    scale; the bound is three times that."""
+    print(f"cic forms B={B} C={C} S={S} {H}x{Wf} offset {offset}", flush=True)
+    rng = _rng("cic forms", B, C, S, H, Wf)
+
+    def put(a):
+        t = torch.empty(a.size + offset, dtype=torch.complex64, device="cuda")[offset:].view(a.shape)
+        return t.copy_(torch.from_numpy(a))
+
+    X, K, gY = _crand(rng, (B, C, H, Wf)), _crand(rng, (S, H, Wf)), _crand(rng, (B, S, H, Wf))
+    Xd, Kd, gYd = put(X), put(K), put(gY)
+    X64, K64, g64 = X.astype(np.complex128), K.astype(np.complex128), gY.astype(np.complex128)
+    assert_parity(to_np(layers.cic_forward(Xd, Kd)), fdc.cic(X64, K64), "cic", rel=2e-6)
+    gX, gK = layers.cic_backward(gYd, Xd, Kd)
+    rgX, rgK = fdc.cic_backward(g64, X64, K64)
+    assert_parity(to_np(gX), rgX, "cic gX", rel=2e-6)
+    assert_parity(to_np(gK), rgK, "cic gK", rel=2e-6)
+    only_x, _ = layers.cic_backward(gYd, Xd, Kd, need_gk=False)
+    _, only_k = layers.cic_backward(gYd, Xd, Kd, need_gx=False)
+    assert torch.equal(gX, only_x) and torch.equal(gK, only_k)
+
+
+@pytest.mark.parametrize("count,H,W,Mh,Mw", [(1, 2, 2, 2, 2), (3, 6, 2, 2, 2), (66000, 4, 6, 2, 4),
+                                             (2, 512, 34, 256, 32)])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_fdp_forms(count, H, W, Mh, Mw, offset):
+    """Pairs of bins that wrap to the next row, more planes than a grid holds, tensors off 16 bytes."""
+    rng = _rng("fdp forms", count, H, W, Mh, Mw)
+    X, gY = _crand(rng, (count, H, W // 2 + 1)), _crand(rng, (count, Mh, Mw // 2 + 1))
+    Y = torch.full((count * Mh * (Mw // 2 + 1) + offset,), 9.0, dtype=torch.complex64, device="cuda")[offset:]
+    gX = torch.full((X.size + offset,), 9.0, dtype=torch.complex64, device="cuda")[offset:]
+    Xd, gYd = _gpu(X), _gpu(gY)
+    layers.call("fdp_forward", layers._ptr(Xd), layers._ptr(Y), count, H, W, Mh, Mw, layers._stream())
+    layers.call("fdp_backward", layers._ptr(gYd), layers._ptr(gX), count, H, W, Mh, Mw, layers._stream())
+    np.testing.assert_array_equal(to_np(Y).reshape(gY.shape), fdc.fdp(X.astype(np.complex128), Mh, Mw).astype(np.complex64))
+    np.testing.assert_array_equal(to_np(gX).reshape(X.shape),
+                                  fdc.fdp_backward(gY.astype(np.complex128), H, W).astype(np.complex64))
