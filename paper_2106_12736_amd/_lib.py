@@ -120,7 +120,7 @@ def lib():
 
 def call(name, *args):
     """Call an fdc entry point that returns a status; raise FdcError unless FDC_OK."""
-    st = getattr(lib(), name)(*args)
+    st = getattr(_lib or lib(), name)(*args)
     if st != FDC_OK:
         raise FdcError(st, name, lib().fdc_last_error().decode())
     return st
