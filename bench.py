@@ -204,7 +204,9 @@ def fused_bwd_launches(wl, input_grad=False, ranges=None, tail=-1, kept=False):
         B, C, S, N, M, L, NF = layer_dims(wl, i)
         if tail >= 0 and i >= tail:
             if i == tail + 1:
-                out += tail_launches(wl, tail, input_grad, kept)[1]
+                late = tail_launches(wl, tail, input_grad, kept)[1]
+                # the tail's dK sums join the launch that adds the ranges of the layer before it
+                out += late if tail == 0 or ranges[tail - 1] <= 1 else late[:1]
             continue
         if i == n - 1:
             out.append((f"row_r2c_{M}", F32 * B * S * M * M + C64 * B * S * M * L))
@@ -215,7 +217,10 @@ def fused_bwd_launches(wl, input_grad=False, ranges=None, tail=-1, kept=False):
             (_, gk_bytes), = gk_launches(B, C, S, N, M, L, NF, 1, zeros=not kept)
             out.append((f"col_bwd_dk_dx_{N}_{M}", gk_bytes + gx_bytes))
         else:
-            out += gk_launches(B, C, S, N, M, L, NF, ranges[i], zeros=not kept and not zeros_early(i))
+            gk = gk_launches(B, C, S, N, M, L, NF, ranges[i], zeros=not kept and not zeros_early(i))
+            if tail >= 1 and i == tail - 1 and ranges[i] > 1:
+                gk[-1] = (gk[-1][0], gk[-1][1] + late[1][1])
+            out += gk
             if dx:
                 out.append((f"col_bwd_gx_{N}_{M}", gx_bytes))
         if dx:

@@ -166,8 +166,15 @@ hipError_t launch_col_fwd_cic(int n, int m, const float2 *T, const float2 *K, fl
 // zeros = false: the dropped bins of gK are left as they are (an earlier launch of the
 // same call wrote their zeros, or the caller's buffer holds them).
 int gk_batch_ranges(int n, int m, int B, int S, long long part_elems);
+// also (2 sums or NULL): further sums, added by the launch that adds the ranges.
+struct GkSum {  // gK [S][N][N/2+1] from partial sums part [BG][S][M][M/2+1]; kept != 0: the kept bins only
+  const float2 *part;
+  float2 *gK;
+  int BG, S, M, N, kept;
+};
 hipError_t launch_col_bwd_gk(int n, int m, const float2 *Tg, const float2 *Xh, float2 *gK, int B, int C,
-                             int S, float2 *part, long long part_elems, hipStream_t s, bool zeros = true);
+                             int S, float2 *part, long long part_elems, hipStream_t s, bool zeros = true,
+                             const GkSum *also = nullptr);
 hipError_t launch_col_bwd_gx(int n, int m, const float2 *Tg, const float2 *K, float2 *V, int B, int C, int S,
                              hipStream_t s);
 // gK [S][N][N/2+1] from BG partial sums part [BG][S][M][M/2+1] (plain layout): at the

@@ -899,20 +899,14 @@ __global__ __launch_bounds__(CT *ColCfg<M>::TPS *BP) void k_col_bwd_gk(const flo
 }
 
 // gK [S][N][N/2+1] from BG partial sums part [BG][S][M][M/2+1] (plain layout), for
-// one or two reductions (grid.y selects the GkSum): a thread per gK element, its BG
+// one to three reductions (grid.y selects the GkSum): a thread per gK element, its BG
 // partial sums loaded together (16 at a time) and added in order at the kept bins,
 // exact zeros elsewhere.  Consecutive threads take consecutive bins of a row.
 // kept != 0: a thread per kept bin only, the other bins of gK left as they are.
-struct GkSum {
-  const float2 *part;
-  float2 *gK;
-  int BG, S, M, N, kept;
-};
-
 constexpr int kGkReduceThreads = 256;
 
-__global__ __launch_bounds__(kGkReduceThreads) void k_gk_reduce(GkSum d0, GkSum d1) {
-  const GkSum d = blockIdx.y == 0 ? d0 : d1;
+__global__ __launch_bounds__(kGkReduceThreads) void k_gk_reduce(GkSum d0, GkSum d1, GkSum d2) {
+  const GkSum d = blockIdx.y == 0 ? d0 : (blockIdx.y == 1 ? d1 : d2);
   const int L = d.M / 2 + 1, nf = d.N / 2 + 1;
   // 32-bit element arithmetic: the launchers keep S * N * (N/2+1) below 2^31
   const unsigned total = (unsigned)(d.kept ? d.S * d.M * L : d.S * d.N * nf);
@@ -960,12 +954,13 @@ static long long gk_reduce_items(const GkSum &d) {
   return d.kept ? (long long)d.S * d.M * (d.M / 2 + 1) : (long long)d.S * d.N * (d.N / 2 + 1);
 }
 
-static hipError_t gk_reduce(const GkSum &d0, const GkSum *d1, hipStream_t s) {
-  long long total = gk_reduce_items(d0);
-  if (d1) total = std::max(total, gk_reduce_items(*d1));
+static hipError_t gk_reduce(std::initializer_list<GkSum> d, hipStream_t s) {
+  long long total = 0;
+  for (const GkSum &g : d) total = std::max(total, gk_reduce_items(g));
   const unsigned gx = (unsigned)std::min<long long>((total + kGkReduceThreads - 1) / kGkReduceThreads, 1 << 16);
-  const char *nm = "gk_reduce";
-  return timed_launch(nm, k_gk_reduce, dim3(gx, d1 ? 2 : 1), dim3(kGkReduceThreads), 0, s, d0, d1 ? *d1 : d0);
+  const GkSum *g = d.begin(), *last = d.end() - 1;
+  return timed_launch("gk_reduce", k_gk_reduce, dim3(gx, (unsigned)d.size()), dim3(kGkReduceThreads), 0, s, g[0],
+                      g + 1 <= last ? g[1] : *last, *last);
 }
 
 template <int N, int M>
@@ -1611,7 +1606,7 @@ int gk_batch_ranges(int n, int m, int B, int S, long long part_elems) {
 }
 
 hipError_t launch_col_bwd_gk(int n, int m, const float2 *Tg, const float2 *Xh, float2 *gK, int B, int C, int S,
-                             float2 *part, long long part_elems, hipStream_t s, bool zeros) {
+                             float2 *part, long long part_elems, hipStream_t s, bool zeros, const GkSum *also) {
   hipError_t err = hipErrorInvalidValue;
   if (!cic_pair_supported(n, m)) return err;
   const long long pe = part ? part_elems : 0;
@@ -1632,8 +1627,12 @@ hipError_t launch_col_bwd_gk(int n, int m, const float2 *Tg, const float2 *Xh, f
       go(std::integral_constant<int, col_ct_for(4, L)>{});
     else
       go(std::integral_constant<int, col_ct_for(gk_ct<M>(), L)>{});
-    if (err != hipSuccess || BG == 1) return;
-    err = gk_reduce(GkSum{part, gK, BG, S, M, n, zeros ? 0 : 1}, nullptr, s);
+    if (err != hipSuccess) return;
+    const GkSum own{part, gK, BG, S, M, n, zeros ? 0 : 1};
+    if (BG > 1)
+      err = also ? gk_reduce({own, also[0], also[1]}, s) : gk_reduce({own}, s);
+    else if (also)
+      err = gk_reduce({also[0], also[1]}, s);
   });
   return err;
 }
@@ -1641,8 +1640,8 @@ hipError_t launch_col_bwd_gk(int n, int m, const float2 *Tg, const float2 *Xh, f
 hipError_t launch_gk_reduce2(const float2 *part0, float2 *gK0, int S0, int M0, int N0, const float2 *part1,
                              float2 *gK1, int S1, int M1, int N1, int BG, hipStream_t s, bool zeros) {
   const int kept = zeros ? 0 : 1;
-  const GkSum d1{part1, gK1, BG, S1, M1, N1, kept};
-  return gk_reduce(GkSum{part0, gK0, BG, S0, M0, N0, kept}, part1 ? &d1 : nullptr, s);
+  const GkSum d0{part0, gK0, BG, S0, M0, N0, kept}, d1{part1, gK1, BG, S1, M1, N1, kept};
+  return part1 ? gk_reduce({d0, d1}, s) : gk_reduce({d0}, s);
 }
 
 hipError_t launch_col_bwd_dk_dx(int n, int m, const float2 *Tg, const float2 *Xh, const float2 *K, float2 *gK,
