@@ -635,7 +635,7 @@ __global__ __launch_bounds__(CT *ColCfg<N>::TPS) void k_col_fwd_crop(const float
 // Output channels of one input channel handled by one workgroup of the CIC inverse
 // kernel (a divisor of J): the pooled input column is loaded once for all of them.
 constexpr int kCicJW = 4;
-// CIC inverse grids below this many workgroups switch to 8-column tiles.
+// CIC inverse grids below this many workgroups take one output channel each, in 8-column tiles.
 constexpr unsigned kCicNarrowGrid = 256;
 
 template <int N, int M, int CT, int JW>
@@ -1544,14 +1544,18 @@ hipError_t launch_col_fwd_cic(int n, int m, const float2 *T, const float2 *K, fl
     auto go = [&](auto kern) {
       err = launch(n2.c_str(), kern, g2, CTM * ColCfg<M>::TPS, lds2, s, Xh, K, U, B, C, J, (int)groups);
     };
-    // Few planes (a small batch at the first layer): 8-column tiles, up to four times the
-    // workgroups, when the default tiles would leave most compute units idle.
-    constexpr int CTS = 8;
-    if (CTS < CTM && jw == kCicJW && g2 < kCicNarrowGrid) {
-      const unsigned g3 = col_grid(groups, L, CTS);
+    // Few planes (a small batch at the first layer): an output channel per workgroup and
+    // 8-column tiles when the default grid would leave most compute units idle; each then
+    // reads the pooled column again, from L2.  One image, 1 -> 8 channels, 1024 -> 512:
+    // 66 -> 264 workgroups, inference of that stack 78.4 -> 74.4 us; 4 images, 1 -> 8 channels,
+    // 512 -> 256: a training step 132.9 -> 127.2 us (four channels in 8-column tiles before).
+    constexpr int CTS = CTM < 8 ? CTM : 8;
+    if (jw == kCicJW && g2 < kCicNarrowGrid) {
+      const long long each = (long long)B * C * J;
+      const unsigned g3 = col_grid(each, L, CTS);
       const size_t lds3 = (twiddle_lds_elems<M>() + lds_size<kColLds>(M * CTS)) * sizeof(float2);
-      err = launch(n2.c_str(), k_col_cic_inv<N, M, CTS, kCicJW>, g3, CTS * ColCfg<M>::TPS, lds3, s, Xh, K, U, B, C, J,
-                   (int)groups);
+      err = launch(n2.c_str(), k_col_cic_inv<N, M, CTS, 1>, g3, CTS * ColCfg<M>::TPS, lds3, s, Xh, K, U, B, C, J,
+                   (int)each);
       return;
     }
     switch (jw) {

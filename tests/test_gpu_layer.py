@@ -135,6 +135,22 @@ def test_small_layer(N, M, B, C, J, artifact, kn):
     assert np.all(to_np(gK)[:, ~kept] == 0)
 
 
+@pytest.mark.parametrize("N,M,B,C,J", [(512, 256, 1, 1, 8), (512, 128, 2, 1, 12), (1024, 512, 1, 1, 8),
+                                       (256, 128, 1, 2, 16), (512, 256, 5, 3, 8), (1024, 512, 9, 1, 8)])
+def test_forward_few_planes(N, M, B, C, J):
+    """The CIC inverse with an output channel per workgroup (few planes) and with four (the last
+    two cases).  Four transforms of log2(N) <= 10 roundings and a product, units of 6e-8 adding
+    as a random walk: below 12 u = 7e-7; the bound is four times that."""
+    print(f"few planes N={N} M={M} B={B} C={C} J={J}", flush=True)
+    rng = _rng("few", N, M, B, C, J)
+    x = rng.random((B, C, N, N), dtype=np.float32)
+    K = inputs.spectral_kernels(rng, C * J, N)
+    layer = layers.CicLayer(B, C, C * J, N, M, "none", 1)
+    y = layer.forward(_gpu(x), _gpu(K))
+    ry, _ = fdc.cic_fdp_layer_forward(x.astype(np.float64), K.astype(np.complex128), M, ORACLE_MODE["none"], 1)
+    assert_parity(to_np(y), ry, "y", rel=3e-6)
+
+
 def test_layer_is_deterministic_and_reentrant():
     N, M, B, C, J = 256, 128, 4, 2, 2
     rng = _rng("det")
