@@ -80,31 +80,31 @@ struct ColLanes {
 // ----------------------------------------------------------------------------
 // Packed inverse input of two rows: v[m] = A_k + i B_k at k = t + TPS m, the Hermitian
 // extensions of the rows' first LIN bins, bin(row 0 or 1, k), weighted by c-weights (a1 at
-// l = 0 and N/2, a1 b1 elsewhere), with real-part semantics at l = 0 and N/2.  Which elements
-// are bins, conjugated bins or zero is known at compile time but for lane t = 0 at the ends.
+// l = 0 and N/2, a1 b1 elsewhere), with real-part semantics at l = 0 and N/2: the imaginary
+// parts there are left out, not multiplied by zero, whatever they hold.  Which elements are
+// bins, conjugated bins or zero is known at compile time but for lane t = 0 at the ends.
 template <int N, int LIN, class Bin>
 __device__ __forceinline__ void c2r_in(float2 (&v)[Plan<N>::E], Bin bin, int t, float a1, float b1) {
   constexpr int TPS = Plan<N>::TPS, E = Plan<N>::E, Q = (LIN - 1) / TPS;  // Q whole groups of TPS bins
   static_assert(Q * TPS == LIN - 1 && 2 * Q <= E, "bins in whole groups of the row plan");
   const float w = a1 * b1;
   const bool t0 = t == 0;
-  // weights of the edge bins, lane t = 0
-  const float er = t0 ? a1 : w, ei = t0 ? 0.f : w;
+  const float edge_w = t0 ? a1 : w;  // weight of the edge bins, lane t = 0
   static_for<0, E>([&](auto mc) {
     constexpr int m = decltype(mc)::value;
+    constexpr bool edge = m == 0 || 2 * m == E;
+    const float wr = edge ? edge_w : w;
     if constexpr (m < Q) {  // bin t + TPS m
       const float2 a = bin(0, t + TPS * m), b = bin(1, t + TPS * m);
-      const float wr = m == 0 ? er : w, wi = m == 0 ? ei : w;
-      v[m] = make_float2(fmaf(-wi, b.y, wr * a.x), fmaf(wr, b.x, wi * a.y));
+      const float ai = edge && t0 ? 0.f : a.y, bi = edge && t0 ? 0.f : b.y;
+      v[m] = make_float2(fmaf(-w, bi, wr * a.x), fmaf(wr, b.x, w * ai));
     } else if constexpr (m >= E - Q) {  // bin N - t - TPS m, conjugated (N/2 itself: m = E/2, t = 0)
       const float2 a = bin(0, N - TPS * m - t), b = bin(1, N - TPS * m - t);
-      const bool edge = 2 * m == E;
-      const float wr = edge ? er : w, wi = edge ? ei : w;
-      v[m] = make_float2(fmaf(wi, b.y, wr * a.x), fmaf(wr, b.x, -(wi * a.y)));
+      const float ai = edge && t0 ? 0.f : a.y, bi = edge && t0 ? 0.f : b.y;
+      v[m] = make_float2(fmaf(w, bi, wr * a.x), fmaf(wr, b.x, -(w * ai)));
     } else if constexpr (m == Q) {  // lane t = 0: bin LIN - 1 < N/2
       const float2 a = bin(0, LIN - 1), b = bin(1, LIN - 1);
-      const float u = t0 ? w : 0.f;
-      v[m] = make_float2(u * (a.x - b.y), u * (a.y + b.x));
+      v[m] = t0 ? make_float2(w * (a.x - b.y), w * (a.y + b.x)) : make_float2(0.f, 0.f);
     } else {
       v[m] = make_float2(0.f, 0.f);
     }

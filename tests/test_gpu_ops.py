@@ -208,3 +208,16 @@ def test_fdp_forms(count, H, W, Mh, Mw, offset):
     np.testing.assert_array_equal(to_np(Y).reshape(gY.shape), fdc.fdp(X.astype(np.complex128), Mh, Mw).astype(np.complex64))
     np.testing.assert_array_equal(to_np(gX).reshape(X.shape),
                                   fdc.fdp_backward(gY.astype(np.complex128), H, W).astype(np.complex64))
+
+
+@pytest.mark.parametrize("n", [16, 32, 64])
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+def test_irfft2_ignores_imaginary_edge_bins(n, value):
+    """Real-part semantics: the imaginary part of the DC row's bins 0 and n/2 is only ever added
+    to imaginary parts of columns 0 and n/2, which the inverse leaves out whatever they hold."""
+    X = _crand(_rng("edge bins", n), (3, n, n // 2 + 1))
+    plan = layers.FftPlan(3, n, n)
+    want = plan.irfft2(_gpu(X))
+    X[1, 0, 0] = complex(X[1, 0, 0].real, value)
+    X[2, 0, n // 2] = complex(X[2, 0, n // 2].real, value)
+    assert torch.equal(plan.irfft2(_gpu(X)), want)
