@@ -813,18 +813,22 @@ __global__ __launch_bounds__(kGwThreads) void k_full_gw(SpecLayout G, SpecLayout
 
 // dL/dw from the partial sums: a workgroup owns PP (s, c) pairs; its 256 / PP thread groups
 // take the chunks in turn, apply the row phases, and their sums are added in order.  PP = 8
-// where 32 would leave few workgroups (64 -> 64 channels: 128 workgroups, 40 us).
+// where 32 would leave few workgroups (64 -> 64 channels: 128 workgroups, 40 us).  The sums
+// are kept in 64 bits: up to 514 chunks added one after the other in 32 made the error of dL/dw
+// 3 to 9 % larger than sums by 16 accumulators had it (128^2, 9 images, 3 x 3 taps: 2.52e-7,
+// 2.70e-7, now 2.30e-7 of which 1.95e-7 are the transforms').  It costs 2 to 4 us: 16 images of
+// 224^2, 64 x 64 channels 14.3 -> 16.1 us, 4 of 128^2, 128 x 128, 5 x 5 taps 14.0 -> 18.4 us.
 template <int NK, int PP>
 __global__ __launch_bounds__(256) void k_full_gw_reduce(const float *__restrict__ part, const float2 *__restrict__ tw,
                                                         float *__restrict__ gw, long long pairs, int P, int ls) {
   constexpr int T = NK * NK, R = gw_record(NK);
   constexpr int GR = 256 / PP;
-  __shared__ float red[GR][PP][T + 1];
+  __shared__ double red[GR][PP][T + 1];
   const int H = P / 2, o = threadIdx.x % PP, w = threadIdx.x / PP, chunks = (H + 2) * ls;
   const long long i = (long long)blockIdx.x * PP + o, ii = i < pairs ? i : pairs - 1;
-  float acc[T];
+  double acc[T];
 #pragma unroll
-  for (int t = 0; t < T; ++t) acc[t] = 0.f;
+  for (int t = 0; t < T; ++t) acc[t] = 0.;
 #pragma unroll 4
   for (int c = w; c < chunks; c += GR) {
     const float *p = part + ((long long)c * pairs + ii) * R;
@@ -838,8 +842,8 @@ __global__ __launch_bounds__(256) void k_full_gw_reduce(const float *__restrict_
         const float2 u = a ? tw[(k * a) % P] : make_float2(1.f, 0.f);
 #pragma unroll
         for (int b = 0; b < NK; ++b) {
-          acc[a * NK + b] = fmaf(u.x, v[b], acc[a * NK + b]);
-          if (a) acc[a * NK + b] = fmaf(u.y, v[R > 1 ? NK + b : 0], acc[a * NK + b]);
+          acc[a * NK + b] = fma((double)u.x, (double)v[b], acc[a * NK + b]);
+          if (a) acc[a * NK + b] = fma((double)u.y, (double)v[R > 1 ? NK + b : 0], acc[a * NK + b]);
         }
       }
     } else {
@@ -855,10 +859,10 @@ __global__ __launch_bounds__(256) void k_full_gw_reduce(const float *__restrict_
   for (int e = threadIdx.x; e < PP * T; e += 256) {
     const int oo = e / T, t = e - oo * T;
     if ((long long)blockIdx.x * PP + oo >= pairs) break;
-    float s = red[0][oo][t];
+    double s = red[0][oo][t];
 #pragma unroll
     for (int q = 1; q < GR; ++q) s += red[q][oo][t];
-    gw[((long long)blockIdx.x * PP + oo) * T + t] = s;
+    gw[((long long)blockIdx.x * PP + oo) * T + t] = (float)s;
   }
 }
 

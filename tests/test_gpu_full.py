@@ -14,7 +14,7 @@ import numpy as np
 import pytest
 import torch
 
-from _parity import assert_parity, to_np
+from _parity import assert_parity, rel_l2, to_np
 from oracle import dft, fdc
 from paper_2106_12736_amd import inputs, layers
 
@@ -213,3 +213,38 @@ def test_full_layer_workload_sampled(wl):
     scale = float(np.sqrt((to_np(y).astype(np.float64) ** 2).sum() * (g64 ** 2).sum()))
     assert abs(ww - yy) <= 1e-4 * scale, ("<gw, w> != <gy, y>", ww, yy, scale)
     assert abs(xx - yy) <= 1e-4 * scale, ("<gx, x> != <gy, y>", xx, yy, scale)
+
+
+@pytest.mark.parametrize("B,n", [(9, 3), (8, 2), (4, 5)])
+def test_full_weight_gradient_rounding(B, n):
+    """dL/dw is off by little more than the rounding of the float32 transforms it is formed from,
+    which is measured here: the same sums in float64 over float32 spectra.  Products and sums
+    add up to 2 B roundings a bin (twice that in the three-product form) and 2 P / 8 in a wave's
+    columns, 2 (2 B) / 2 + 32 / 2 <= 34 as partial sums grow like a random walk, of 2.5e-8 each
+    (root mean square of 2^-24 over a binade): below 1.5e-7.  Row pairs added up in float32
+    as well gave 1.6e-7 to 1.9e-7."""
+    C, S, P = 24, 40, 128
+    whole = alone = 0.0
+    for seed in range(2):
+        rng = _rng("gw rounding", B, n, seed)
+        x, gy = inputs.normal(rng, (B, C, P, P)), inputs.normal(rng, (B, S, P, P))
+        w = inputs.he_normal_weights(rng, S, C, n)
+        layer = layers.FullLayer(B, C, S, P, kernel_n=n, artifact="roll")
+        saved = layer.new_saved()
+        layer.forward(_gpu(x), _gpu(w), saved=saved)
+        gw = to_np(layer.backward(_gpu(gy), saved, _gpu(w))[1])
+        shift = ((n - 1) // 2, (n - 1) // 2)
+        rolled = np.roll(gy, shift, (-2, -1))
+
+        def sums(X, G):
+            D = np.matmul(G.reshape(B, S, -1).transpose(2, 1, 0), X.reshape(B, C, -1).transpose(2, 0, 1).conj())
+            return np.fft.irfft2(D.transpose(1, 2, 0).reshape(S, C, P, P // 2 + 1))[..., :n, :n]
+
+        ref = sums(np.fft.rfft2(x.astype(np.float64)), np.fft.rfft2(rolled.astype(np.float64)))
+        X, G = (to_np(layers.FftPlan(B * k, P, P).rfft2(_gpu(t))).reshape(B, k, P, P // 2 + 1).astype(np.complex128)
+                for t, k in ((x, C), (rolled, S)))
+        whole += rel_l2(gw, ref) / 2
+        alone += rel_l2(sums(X, G), ref) / 2
+    added = np.sqrt(max(0.0, whole**2 - alone**2))
+    print(f"dL/dw B={B} n={n}: {whole:.3e}, transforms {alone:.3e}, sums {added:.3e}", flush=True)
+    assert added < 1.5e-7
