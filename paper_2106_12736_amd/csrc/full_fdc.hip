@@ -24,6 +24,7 @@
 // A[l % 16][l / 16], B[l / 16][l % 16] and D[4 (l / 16) + j][l % 16] in register j.
 #include "device.h"
 #include "internal.h"
+#include "lds_limit.h"
 
 #include <hip/hip_runtime.h>
 
@@ -1032,10 +1033,7 @@ hipError_t launch_full_gw(int nk, SpecLayout G, SpecLayout X, const float2 *tw, 
       constexpr bool kGauss = IMG == 8 && NK <= 3;
       constexpr size_t lds = (size_t)2 * GwStage<IMG>::BUF * sizeof(float2);
       static_assert(lds <= 160 * 1024 && lds >= (size_t)3 * 256 * 8 * NK * sizeof(float), "dL/dw: LDS");
-      static const hipError_t attr =
-          hipFuncSetAttribute(reinterpret_cast<const void *>(k_full_gw<NK, IMG, kGauss>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      err = attr;
+      err = allow_lds<k_full_gw<NK, IMG, kGauss>>(lds);
       if (err != hipSuccess) return;
       err = timed_launch("full_gw", k_full_gw<NK, IMG, kGauss>, dim3((unsigned)grid), dim3(kGwThreads), lds, s, G, X,
                          tw, part, B, S, C, P, ls);

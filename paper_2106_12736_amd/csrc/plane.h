@@ -7,6 +7,7 @@
 #include "device.h"
 #include "fft.h"
 #include "internal.h"
+#include "lds_limit.h"
 
 #include <hip/hip_runtime.h>
 
@@ -173,13 +174,5 @@ __host__ __device__ constexpr int row_scratch(int items) {
 }
 
 }  // namespace plane
-
-// Raise a kernel's dynamic LDS limit to `bytes` (once per kernel).
-template <auto Kern>
-static hipError_t allow_lds(size_t bytes) {
-  static const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(Kern),
-                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-  return e;
-}
 
 }  // namespace fdc
