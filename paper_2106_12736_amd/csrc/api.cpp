@@ -556,7 +556,7 @@ fdc_status fdc_cic_layer_forward(const fdc_layer_plan *p, const float *x, const 
   if (!x || !K || !y) return fail(FDC_EINVAL, "NULL tensor");
   if (fdc_status st = check_ws(ws, ws_bytes, p->fwd_ws)) return st;
   const int B = p->B, C = p->C, S = p->S, N = p->N, M = p->M, L = M / 2 + 1;
-  if (fdc::small_layer_supported(N, M)) {
+  if (fdc::small_fwd_supported(N, M, B, C, S)) {
     const fdc::SpecLayout none{};
     return check_hip(fdc::launch_small_fwd(N, M, x, reinterpret_cast<const float2 *>(K),
                                            saved ? fdc::tiled_layout(static_cast<const float2 *>(saved),
@@ -1301,7 +1301,7 @@ fdc_status fdc_cic_layer_dk_ranges(const fdc_layer_plan *p, int *ranges) {
   if (fdc_status st = check_layer_plan(p, 0)) return st;
   if (ranges == nullptr) return fail(FDC_EINVAL, "ranges is NULL");
   if (fdc::small_bwd_supported(p->N, p->M, p->B, p->C, p->S)) {
-    *ranges = fdc::small_bwd_ranges(p->M, p->B, p->C, p->S);
+    *ranges = fdc::small_bwd_ranges(p->N, p->M, p->B, p->C, p->S);
     return FDC_OK;
   }
   // the same scratch as fdc_cic_layer_backward: the dX buffer

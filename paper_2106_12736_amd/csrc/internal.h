@@ -200,11 +200,12 @@ hipError_t launch_col_bwd_dk_dx(int n, int m, const float2 *Tg, const float2 *Xh
 bool tail_supported(int na, int ma, int mb, int ja, int jb);
 // A whole small layer (n <= 128) in one launch each way (small.hip); `saved` (main NULL: not
 // stored) is the pooled input spectrum, y / gy images are seen through `view`.  The backward
-// takes `part`, scratch of small_bwd_ranges(...) x S x m x (m/2+1) complex values (not used
-// when that is 1 range), for dK's sums over image ranges, which launch_gk_reduce2 adds.
+// takes `part`, scratch of small_bwd_ranges(...) x S x m x (m/2+1) complex values, for dK's
+// sums over image ranges, which launch_gk_reduce2 adds (unused where gK is written at once).
 bool small_layer_supported(int n, int m);
+bool small_fwd_supported(int n, int m, int B, int C, int S);
 bool small_bwd_supported(int n, int m, int B, int C, int S);
-int small_bwd_ranges(int m, int B, int C, int S);
+int small_bwd_ranges(int n, int m, int B, int C, int S);
 hipError_t launch_small_fwd(int n, int m, const float *x, const float2 *K, SpecLayout saved, float *y, ImgView view,
                             long long out_plane, int B, int C, int S, hipStream_t s);
 hipError_t launch_small_bwd(int n, int m, const float *gy, ImgView view, long long out_plane, SpecLayout saved,

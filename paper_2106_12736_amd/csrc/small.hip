@@ -212,12 +212,12 @@ struct SmallBwd {
 //   channels, 32 more registers, spilled and ran 1.6 times longer);
 //   NJ = 0: any J, one image per range (R = B), the products written as they are formed.
 // (Registers: four waves a SIMD, three with dK's sums, which spilled 30 to 60 values at four.)
-// dst (NULL: dK skipped): part [R][S][M][L], or, R == 1, gK [S][N][N/2+1] with zeros at the
-// bins FDP drops.
+// dst (NULL: dK skipped): parts = 1: part [R][S][M][L]; parts = 0 (R == 1): gK [S][N][N/2+1]
+// with zeros at the bins FDP drops.
 template <int N, int M, int JP, int NJ>
 __global__ __launch_bounds__((SmallBwd<N, M, JP>::NT), NJ == 1 ? 3 : 4) void k_small_bwd(
     const float *__restrict__ gy, ImgView view, long long out_plane, SpecLayout saved, const float2 *__restrict__ K,
-    float *__restrict__ gx, float2 *__restrict__ dst, int B, int C, int J, int R) {
+    float *__restrict__ gx, float2 *__restrict__ dst, int B, int C, int J, int R, int parts) {
   using G = SmallBwd<N, M, JP>;
   using PN = Plan<N>;
   using PM = Plan<M>;
@@ -265,7 +265,7 @@ __global__ __launch_bounds__((SmallBwd<N, M, JP>::NT), NJ == 1 ? 3 : 4) void k_s
   for (int m = 0; m < PM::E; ++m) dk[m] = make_float2(0.f, 0.f);
   // dK of output channel o at this thread's column
   auto store_dk = [&](int o, const Col &cl, const float2(&d)[PM::E]) __attribute__((always_inline)) {
-    if (R > 1) {
+    if (parts) {
       float2 *p = dst + ((long long)range * S + o) * M * L + cl.lc;
 #pragma unroll
       for (int m = 0; m < PM::E; ++m) p[(cl.t + PM::TPS * m) * L] = d[m];
@@ -415,7 +415,7 @@ __global__ __launch_bounds__((SmallBwd<N, M, JP>::NT), NJ == 1 ? 3 : 4) void k_s
     const Col cl(loop_tid());
     if (cl.act) store_dk(c * J + cl.q, cl, dk);
   }
-  if (R == 1 && M < N) {  // zeros at the dropped bins of this channel's gK planes
+  if (!parts && M < N) {  // zeros at the dropped bins of this channel's gK planes
     for (int r = threadIdx.x / 64; r < J * N; r += NT / 64) {
       const int o = c * J + r / N, k = r % N;
       const bool keep = k < M / 2 || k >= N - M / 2;
@@ -445,36 +445,172 @@ static bool dispatch_small(int n, int m, F &&f) {
 }
 
 bool small_layer_supported(int n, int m) {
+  // (128 -> 128 has 65 columns of 16 lanes, more than the 1024 threads of a workgroup)
   return dispatch_small(n, m, [](auto, auto) {});
 }
 
-// Where the one-launch backward is the faster one (graph replays of both, us; separate
-// launches -> one launch).  It takes an input channel's output channels in turn, so many of
-// them cost it where the planes are large or already fill the chip:
-//   64 -> 64: J = 1 43 -> 35, J = 2 20 -> 16 and 52 -> 50, J = 4 20 -> 19 at 3 planes but
-//             221 -> 236 at 3000, J = 8 31 -> 40
-//   128 -> 64: J = 1 66 -> 56, J = 2 22 -> 20 at 64 planes but 71 -> 81 at 1024, J = 4 21 -> 30
-//   to 32 points and below: 16 -> 9, 32 -> 18, 20 -> 12 and so on, but 62 -> 70 (32 -> 32) and
-//             76 -> 78 (64 -> 32) at 3000 planes and J = 4
-// The forward is faster at every size (16 planes 11 -> 6, 3000 planes 63 -> 44 at 64 -> 32).
+constexpr int kSmallCus = 256;
+constexpr int kSmallJps = 3;  // backward forms: 1, 2 or 4 output channels at a time
+
+// Workgroups of a form resident at a time: by waves (the kernels' launch bounds) and LDS.  The
+// backward to 64 points counts one a CU: a second one there gains nothing (16 images of 36
+// channels, 64 -> 64: 8 ranges 0.82 of the separate launches, 16 ranges 0.72).
+static int small_slots(int simd_waves, int waves, size_t lds) {
+  return kSmallCus * std::max(1, std::min(4 * simd_waves / waves, (int)(160 * 1024 / lds)));
+}
+struct SmallForms {  // waves of a workgroup and workgroups resident
+  int fwd_slots, bwd_waves[kSmallJps], bwd_slots[kSmallJps];
+};
+static SmallForms small_forms(int n, int m) {
+  SmallForms f{};
+  dispatch_small(n, m, [&](auto nc, auto mc) {
+    constexpr int N = decltype(nc)::value, M = decltype(mc)::value;
+    f.fwd_slots = small_slots(4, SmallFwd<N, M>::WAVES, SmallFwd<N, M>::END * sizeof(float2));
+    auto bwd = [&](auto jpc, int i) {
+      using G = SmallBwd<N, M, decltype(jpc)::value>;
+      f.bwd_waves[i] = G::WAVES;
+      f.bwd_slots[i] = M == 64 ? kSmallCus : small_slots(3, G::WAVES, G::END * sizeof(float2));
+    };
+    bwd(Int<1>{}, 0);
+    if constexpr (M <= 32) bwd(Int<2>{}, 1), bwd(Int<4>{}, 2);
+  });
+  return f;
+}
+
+// Output channels a workgroup of the forward takes: each workgroup transforms its input plane
+// again, so few channels a workgroup pay only while the launch is short of workgroups.
+//   128 points (one or two workgroups a CU): the least (2 + JL) (rounds + w / 512) for w
+//     workgroups in `rounds` rounds of the resident ones, a plane's own transforms counted as 2
+//     channels: within 1 % of the best JL on average over 2 to 12 channels and 1 to 4096 planes,
+//     22 % at worst.  (The rule below took up to 2.2 times the best: 448 planes of 5 channels,
+//     128 -> 64: 47 us on separate launches, 78 with JL = 1, 38 with JL = 5.)
+//   smaller planes: the most with at least 512 workgroups (1024 for 32 points and 8 channels or
+//     more: 512 planes of 8, 32 -> 8: 12.3 us with JL = 8, 9.1 with 4, 11.8 on separate
+//     launches); half of J where all of J would start a nearly empty second round (1040 planes of
+//     12, 64 -> 16: 41.8 us with JL = 12, 36.6 with 6, 37.9 on separate launches).
+static int small_jl(int n, int m, long long planes, int J) {
+  const int slots = small_forms(n, m).fwd_slots;
+  int JL = J;
+  if (n == 128) {
+    double least = 0.;
+    auto consider = [&](int jl) {
+      const long long w = planes * (J / jl);
+      const double cost = (2. + jl) * ((double)((w + slots - 1) / slots) + w / 512.);
+      if (jl == J || cost < least) least = cost, JL = jl;
+    };
+    for (int d = 1; (long long)d * d <= J; ++d)
+      if (J % d == 0) consider(J / d), consider(d);
+    return JL;
+  }
+  const long long target = n == 32 && J >= 8 ? 1024 : 512;
+  for (int d = 2; d <= J && planes * (J / JL) < target; ++d)
+    if (J % d == 0) JL = J / d;
+  if (JL == J && J % 2 == 0 && J >= 8 && n == 64 && m < n && planes > slots && 4 * planes <= 5 * slots) JL = J / 2;
+  return JL;
+}
+
+// Where the one-launch forward is the faster one: everywhere (16 planes 11 -> 6 us, 3000 planes
+// of 64 -> 32 63 -> 44; 64 -> 16 with 8 channels 1.04 to 1.07 at 528 and 1040 planes) but for 128 -> 64 and 128 -> 32 with a last round of workgroups that is
+// nearly empty, against separate launches that share the pooled columns between an even number
+// of channels (one launch over separate ones, 16 images a call):
+//   128 -> 64, 256 workgroups a round: 320 planes J = 4, 6, 8, 12: 1.02 to 1.08; 576 planes J = 2,
+//     4, 6, 8: 1.02 to 1.08, but J = 3, 5, 12: 0.95, 0.96, 0.83; 1040 planes J = 1, 2: 1.04, 1.10,
+//     J = 3 to 8: 0.99 to 0.73; full rounds 0.6 to 0.9
+//   128 -> 32, 512 a round: 576 to 704 planes J = 8, 12: 1.00 to 1.06; 1040: 1.02, 1.09; J <= 6: 0.7 to 0.95
+bool small_fwd_supported(int n, int m, int B, int C, int S) {
+  if (!small_layer_supported(n, m)) return false;
+  if (n != 128) return true;
+  const int J = S / C;
+  const long long planes = (long long)B * C;
+  if (m == 64) {
+    const double full = planes / (256. * ((planes + 255) / 256));  // share of the rounds at JL = J
+    if (planes > 1024) return J > 2 || full >= 0.9;
+    return J % 2 != 0 || full >= 0.8 || planes <= 256 || (planes > 512 && J > 8);
+  }
+  return J < 8 || planes <= 512 || planes > 1536 || planes / (512. * ((planes + 511) / 512)) >= 0.72;
+}
+
+// How the backward of a layer runs: JP output channels at a time, NJ = 1 where that is all of
+// them (0: one image per workgroup), R image ranges, dK through partial sums or straight to gK.
+struct SmallPlan {
+  int JP, NJ, R, parts;
+};
+static SmallPlan small_plan(int n, int m, int B, int C, int J) {
+  const SmallForms f = small_forms(n, m);
+  const long long planes = (long long)B * C;
+  SmallPlan p{1, 0, B, 1};
+  // Channels side by side in LDS, 4 or 2: one at a time they are a chain of J turns, and each
+  // turn reads the plane's stages again (64 -> 16, 1040 planes of 8: 33 us, 57 with one, 38 on
+  // separate launches; 32 -> 8, 512 planes of 12: 17, 37, 22).  Two at 32 points with enough
+  // planes, where four leave two workgroups a CU (64 -> 32, 576 planes of 4: 24 us, 30 with four).
+  if (m <= 32 && J % 2 == 0) {
+    p.JP = J % 4 == 0 ? 4 : 2;
+    if (p.JP == 4 && m == 32 && n <= 64 && planes >= (J == 4 ? 320 : 576)) p.JP = 2;
+  }
+  const int form = p.JP / 2;  // 1, 2, 4 -> 0, 1, 2
+  p.NJ = J == p.JP ? 1 : 0;
+  if (p.NJ > 0 && B > 1) {
+    // Images a range, all or a power of two: the least of rounds x images + what adding the ranges
+    // costs, in units of one image's stages (within 0.4 % of the best power of two on average,
+    // 29 % at worst; a fixed 1024 workgroups: 4 %, 90 %: 128 -> 32, 2 x 160 planes of 4: 47 us with 2
+    // ranges, 28 with 1).
+    const int slots = f.bwd_slots[form];
+    double least = (double)((C + slots - 1) / slots) * B;
+    p.R = 1;
+    for (long long images = 1; images < B; images *= 2) {
+      const long long R = (B + images - 1) / images, w = C * R;
+      const double cost = (double)((w + slots - 1) / slots) * images + 0.75 + 0.4 * w / slots;
+      if (cost < least) least = cost, p.R = (int)R;
+    }
+  }
+  // One range writes gK itself unless too few threads would write its zeros (32 -> 8, one plane of
+  // 8 channels: 29 us, 11 through partial sums and the launch that adds them)
+  if (p.R == 1) {
+    const int waves = f.bwd_waves[form];
+    const long long zeros = (long long)J * ((long long)n * (n / 2 + 1) - (long long)m * (m / 2 + 1));
+    p.parts = n > m && zeros > (waves >= 4 ? 16 : 8) * 64 * waves && (long long)C * waves * waves < 1024;
+  }
+  return p;
+}
+
+// Where the one-launch backward is the faster one (graph replays of both; one launch over
+// separate ones, 1 to 16 images, 1 to 4096 planes):
+//   to 32 points and below, J = 1, 2, 4 and even J: 0.3 to 1.0, but 128 -> 32 below
+//   J = 3: 0.3 to 0.95, but 64 -> 16 past 1024 planes 1.05 at 2 images, 1.16 at 4096 planes
+//   odd J from 5 go one at a time; J = 5: 32 -> 32, 64 -> 32, 32 -> 16 up to 1.7 below 320 planes, 0.4 to
+//     0.95 from there (64 -> 32 1.08 to 1.12 past 1024); 32 -> 8, 64 -> 16 1.03 to 1.24
+//   128 -> 32: at 2 images 64 to 704 channels of J = 3, 6, 8, 12 1.03 to 1.19 (two ranges of
+//     partial sums against sums written once); at 16 J = 3 1.06 from 2048 planes, J = 12, 16 1.05 to 1.09
+//     at 576 to 704; J = 5 1.03 to 1.26 but for 16 images and 64 to 512 planes, 0.77 to 0.97
+//   64 -> 64: J = 1, 2 0.3 to 1.0 (J = 2, 16 images of 3072 planes 1.05, but
+//     4096 cropped ones, forward and backward, 306 us against 314); J = 3 0.3 to 1.03 up to 511 planes; J = 4 0.55 to 0.97 from 32 to 511 planes, up to 1.17 elsewhere; J >= 5 up to 1.5
+//   128 -> 64: J = 1 0.4 to 0.9; J = 2 0.43 to 1.0 where the rounds of 256 workgroups are full, 1.03 at 320
+//     planes, 1.05 to 1.24 from 576; J >= 3 up to 2.1
 bool small_bwd_supported(int n, int m, int B, int C, int S) {
   if (!small_layer_supported(n, m)) return false;
   const int J = S / C;
   const long long planes = (long long)B * C;
-  if (m == 64) return J == 1 || (J == 2 && (n == 64 || planes < 512)) || (J <= 4 && n == 64 && planes < 512);
-  return !(m == 32 && n <= 64 && J >= 4 && planes >= 1024);
+  const bool odd = J % 2 != 0 && J > 3;
+  if (m == 64) {
+    if (J == 1) return true;
+    if (n == 128) return J == 2 && (planes <= 256 || (planes >= 416 && planes < 512));
+    return J == 2 || (planes < 512 && (J == 3 || (J == 4 && (planes >= 32 || B == 1))));
+  }
+  if (n == 128) {
+    if (odd) return planes >= 64 && (B == 1 || (B >= 8 && planes <= 512));
+    if (B == 1 || J == 1 || J == 2 || J == 4) return true;
+    if (B < 8) return C < 64 || C > 704;
+    return !(J == 3 && planes >= 1536) && !(J >= 12 && planes > 512 && planes <= 704);
+  }
+  if (odd) return planes >= 320 && ((m == 32 && (n == 32 || planes < 1024)) || (m == 16 && n == 32));
+  if (n == 64 && m == 16 && J == 3 && planes > 1024) return B >= 8 && planes < 3072;
+  return true;
 }
-
-// Workgroups a launch aims for: two per compute unit.
-constexpr long long kSmallWgs = 512;
 
 hipError_t launch_small_fwd(int n, int m, const float *x, const float2 *K, SpecLayout saved, float *y, ImgView view,
                             long long out_plane, int B, int C, int S, hipStream_t s) {
   hipError_t err = hipErrorInvalidValue;
-  const int J = S / C;
-  int JL = J;  // output channels per workgroup: fewer while the launch is short of workgroups
-  for (int d = 2; d <= J; ++d)
-    if (J % d == 0 && (long long)B * C * (J / JL) < kSmallWgs) JL = J / d;
+  const int J = S / C, JL = small_jl(n, m, (long long)B * C, J);
   const long long grid = (long long)B * C * (J / JL);
   if (grid >= (1LL << 31)) return err;
   dispatch_small(n, m, [&](auto nc, auto mc) {
@@ -491,33 +627,17 @@ hipError_t launch_small_fwd(int n, int m, const float *x, const float2 *K, SpecL
   return err;
 }
 
-// How the backward of a layer runs: JP output channels at a time, NJ = 1 where that is all of
-// them (0: one image per workgroup), R image ranges.
-struct SmallPlan {
-  int JP, NJ, R;
-};
-static SmallPlan small_plan(int m, int B, int C, int J) {
-  SmallPlan p{1, 0, B};
-  const bool few = (long long)B * C < kSmallWgs;  // latency counts: channels side by side
-  if (m <= 32 && J % 4 == 0 && (few || J == 4)) p.JP = 4;
-  else if (m <= 32 && J == 2 && few) p.JP = 2;
-  const int nj = J % p.JP == 0 ? J / p.JP : 0;
-  p.NJ = nj == 1 ? 1 : 0;
-  if (p.NJ > 0) p.R = (int)std::min<long long>(B, std::max<long long>(1, (2 * kSmallWgs + C - 1) / C));
-  return p;
-}
-
-int small_bwd_ranges(int m, int B, int C, int S) { return small_plan(m, B, C, S / C).R; }
+int small_bwd_ranges(int n, int m, int B, int C, int S) { return small_plan(n, m, B, C, S / C).R; }
 
 hipError_t launch_small_bwd(int n, int m, const float *gy, ImgView view, long long out_plane, SpecLayout saved,
                             const float2 *K, float *gx, float2 *gK, float2 *part, int B, int C, int S,
                             hipStream_t s) {
   hipError_t err = hipErrorInvalidValue;
   const int J = S / C;
-  const SmallPlan p = small_plan(m, B, C, J);
+  const SmallPlan p = small_plan(n, m, B, C, J);
   const long long grid = (long long)C * p.R;
   if (grid >= (1LL << 31)) return err;
-  float2 *dst = gK == nullptr ? nullptr : (p.R > 1 ? part : gK);
+  float2 *dst = gK == nullptr ? nullptr : (p.parts ? part : gK);
   dispatch_small(n, m, [&](auto nc, auto mc) {
     constexpr int N = decltype(nc)::value, M = decltype(mc)::value;
     static const std::string nm = "small_bwd_" + std::to_string(N) + "_" + std::to_string(M);
@@ -529,7 +649,7 @@ hipError_t launch_small_bwd(int n, int m, const float *gy, ImgView view, long lo
       err = allow_lds<k_small_bwd<N, M, JP, NJ>>(lds);
       if (err != hipSuccess) return;
       err = timed_launch(nm.c_str(), k_small_bwd<N, M, JP, NJ>, dim3((unsigned)grid), dim3(G::NT), lds, s, gy, view,
-                         out_plane, saved, K, gx, dst, B, C, J, p.R);
+                         out_plane, saved, K, gx, dst, B, C, J, p.R, p.parts);
     };
     if constexpr (M <= 32) {
       if (p.JP == 4) {
@@ -538,14 +658,15 @@ hipError_t launch_small_bwd(int n, int m, const float *gy, ImgView view, long lo
         return;
       }
       if (p.JP == 2) {
-        go(Int<2>{}, Int<1>{});
+        if (p.NJ == 1) go(Int<2>{}, Int<1>{});
+        else go(Int<2>{}, Int<0>{});
         return;
       }
     }
     if (p.NJ == 1) go(Int<1>{}, Int<1>{});
     else go(Int<1>{}, Int<0>{});
   });
-  if (err != hipSuccess || gK == nullptr || p.R == 1) return err;
+  if (err != hipSuccess || gK == nullptr || !p.parts) return err;
   return launch_gk_reduce2(part, gK, S, m, n, nullptr, nullptr, 0, 0, 0, p.R, s);
 }
 

@@ -372,6 +372,24 @@ def test_dk_ranges_queries():
     assert _lib.status("fdc_cic_stack_dk_ranges", sp, 0, ctypes.byref(r)) == FDC_EINVAL  # destroyed
 
 
+@pytest.mark.parametrize("N,M,B,C,J,most", [
+    (128, 32, 2, 160, 4, 1),    # one range of two images where two would start a second round of workgroups
+    (64, 16, 16, 65, 5, 2),     # five channels one after the other: separate launches, at most B / 8 ranges
+    (32, 8, 16, 4, 7, 2),
+    (128, 64, 16, 20, 2, 2),    # a second round of workgroups, nearly empty: separate launches
+    (64, 64, 4, 1, 4, 1),
+])
+def test_small_layer_backward_route(N, M, B, C, J, most):
+    """How many image ranges dK is summed in tells the one-launch backward (a range an image, or
+    by rounds of workgroups) from the separate launches; both sides of the rule are measured
+    beside it."""
+    r, lp = ctypes.c_int(), ctypes.c_void_p()
+    assert _lib.status("fdc_cic_layer_plan_create", ctypes.byref(lp), B, C, C * J, N, M, 0, 1) == FDC_OK
+    assert _lib.status("fdc_cic_layer_dk_ranges", lp, ctypes.byref(r)) == FDC_OK
+    assert _lib.status("fdc_layer_plan_destroy", lp) == FDC_OK
+    assert 1 <= r.value <= most
+
+
 def test_head_and_adam_validation():
     """The classifier head and Adam refuse bad sizes and NULL arguments on the host,
     before any launch; the head workspace is one float per (chunk of 1024 features,

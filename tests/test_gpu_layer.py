@@ -221,3 +221,49 @@ def test_stack_full_size(wl):
     gks2 = [g.clone() for g in stack.backward(_gpu(d.grad), Ks)]
     for a, b in zip(gks2, gks):
         assert torch.equal(a, b)
+
+
+# Forms that the number of planes decides: several images a workgroup with an uneven last range
+# (1 and 4 channels at a time; M < N, where the row scratch of one stage lies on the planes of
+# another), two of more channels at a time, a single range through partial sums and straight to
+# gK, and all of an odd number of channels a forward workgroup.
+SMALL_PLANE_CASES = [
+    # N, M, B, C, J, most image ranges
+    (64, 32, 9, 300, 1, 8),
+    (32, 8, 5, 900, 4, 4),
+    (128, 32, 7, 60, 4, 4),
+    (128, 64, 7, 60, 1, 4),
+    (64, 32, 2, 300, 4, 2),
+    (32, 16, 3, 2, 6, 3),
+    (128, 32, 2, 3, 6, 2),
+    (32, 8, 1, 3, 8, 1),
+    (128, 32, 1, 20, 2, 1),
+    (128, 64, 2, 100, 3, 2),
+    (64, 16, 8, 130, 12, 8),
+]
+
+
+@pytest.mark.parametrize("N,M,B,C,J,most", SMALL_PLANE_CASES)
+def test_small_layer_by_planes(N, M, B, C, J, most):
+    """As test_small_layer; at most 9 images more in dK's sums, 3 u of a random walk."""
+    print(f"small layer planes N={N} M={M} B={B} C={C} J={J}", flush=True)
+    rng = _rng("small planes", N, M, B, C, J)
+    x = rng.random((B, C, N, N), dtype=np.float32)
+    K = inputs.spectral_kernels(rng, C * J, N)
+    layer = layers.CicLayer(B, C, C * J, N, M, "none", 1)
+    assert layer.dk_ranges() <= most
+    gy = rng.standard_normal((B, C * J, M, M), dtype=np.float32)
+    xg, Kg, gyg = _gpu(x), _gpu(K), _gpu(gy)
+    saved = layer.new_saved()
+    y = layer.forward(xg, Kg, saved=saved)
+    gx, gK = layer.backward(gyg, saved, Kg)
+    only_x, _ = layer.backward(gyg, None, Kg, need_gk=False)
+    _, only_k = layer.backward(gyg, saved, None, need_gx=False)
+    assert torch.equal(gx, only_x) and torch.equal(gK, only_k)
+    ry, xs = fdc.cic_fdp_layer_forward(x.astype(np.float64), K.astype(np.complex128), M, ORACLE_MODE["none"], 1)
+    rgx, rgK = fdc.cic_fdp_layer_backward(gy.astype(np.float64), xs, K.astype(np.complex128), M, ORACLE_MODE["none"], 1)
+    for got, ref, name in ((y, ry, "y"), (gx, rgx, "gx"), (gK, rgK, "gK")):
+        assert_parity(to_np(got), ref, name, rel=3e-6)
+    kept = np.zeros((N, N // 2 + 1), bool)
+    kept[list(range(M // 2)) + list(range(N - M // 2, N)), : M // 2 + 1] = True
+    assert np.all(to_np(gK)[:, ~kept] == 0)
