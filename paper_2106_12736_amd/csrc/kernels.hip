@@ -1155,43 +1155,65 @@ __global__ __launch_bounds__(256) void k_cic_fwd(const float2 *X, const float2 *
   }
 }
 
+// acc += sum of x(i) conj(y(i)), i = 0 .. n-1 in order, the loads of U terms issued before the
+// first is used.  U = 4 pays where the launch has few waves to hide a load behind (32 images of
+// 32 x 17 bins, gK: 6.3 -> 5.0 us); with many, the fewer streams in flight the better (32 images
+// of 8 channels of 512 x 257 bins, gX: 81 us one by one, 90 by eights).
+template <int V, int U, class X, class Y>
+__device__ __forceinline__ void cic_terms(Bins<V> &acc, int i, X x, Y y) {
+  Bins<V> xs[U], ys[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) xs[u] = x(i + u), ys[u] = y(i + u);
+  if constexpr (U > 1) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+#pragma unroll
+    for (int e = 0; e < V; ++e) acc.v[e] = cfmac(acc.v[e], xs[u].v[e], ys[u].v[e]);
+}
+template <int V, int U, class X, class Y>
+__device__ __forceinline__ void cic_sum(Bins<V> &acc, int n, X x, Y y) {
+  static_assert(U == 1 || U == 2 || U == 4, "remainders of up to 3 terms");
+  int i = 0;
+#pragma unroll 1
+  for (; i + U <= n; i += U) cic_terms<V, U>(acc, i, x, y);
+  if constexpr (U > 2)
+    if (i + 2 <= n) cic_terms<V, 2>(acc, i, x, y), i += 2;
+  if constexpr (U > 1)
+    if (i < n) cic_terms<V, 1>(acc, i, x, y);
+}
+
 // gX[b][c] = sum_j gY[b][c J + j] conj(K[c J + j]), one input channel of one image a turn.
-template <int V>
+template <int V, int U>
 __global__ __launch_bounds__(256) void k_cic_bwd_gx(const float2 *gY, const float2 *K, float2 *gX, int B, int C,
                                                     int J, long long P) {
   FDC_EACH_BINS(p, P, V)
   for (int c = blockIdx.y; c < C; c += gridDim.y) {
+    const float2 *k = K + (long long)c * J * P + p;
     for (int b = blockIdx.z; b < B; b += gridDim.z) {
+      const float2 *g = gY + ((long long)b * C + c) * J * P + p;
       Bins<V> acc{};
-#pragma unroll 4
-      for (int j = 0; j < J; ++j) {
-        const Bins<V> g = bins_load<V>(gY + (((long long)b * C + c) * J + j) * P + p);
-        const Bins<V> k = bins_load<V>(K + ((long long)c * J + j) * P + p);
-#pragma unroll
-        for (int i = 0; i < V; ++i) acc.v[i] = cfmac(acc.v[i], g.v[i], k.v[i]);
-      }
+      cic_sum<V, U>(acc, J, [&](int j) { return bins_load<V>(g + j * P); },
+                    [&](int j) { return bins_load<V>(k + j * P); });
       bins_store<V>(gX + ((long long)b * C + c) * P + p, acc);
     }
   }
 }
 
-// gK[o] = sum_b gY[b][o] conj(X[b][o / J]), b in order.
-template <int V>
+// gK[o] = sum_b gY[b][o] conj(X[b][o / J]), b in order.  The grid runs over all S planes' bins
+// without a break: a block each for the rest of every plane unbalances the few blocks there are
+// (32 images of 8 channels of 128 x 65 bins: 12.1 us then, 6.7 now, one load a time).  I: 32-bit
+// indices where they fit.
+template <int V, int U, class I>
 __global__ __launch_bounds__(256) void k_cic_bwd_gk(const float2 *gY, const float2 *X, float2 *gK, int B, int C,
-                                                    int J, long long P) {
-  const int S = C * J;
-  FDC_EACH_BINS(p, P, V)
-  for (int o = blockIdx.y; o < S; o += gridDim.y) {
-    const int c = o / J;
+                                                    int J, I P) {
+  const I total = (I)C * J * P;
+  for (I i = ((I)blockIdx.x * 256 + threadIdx.x) * V; i < total; i += (I)gridDim.x * 256 * V) {
+    const I o = i / P, p = i - o * P, c = o / J;
+    const float2 *x = X + c * P + p;
     Bins<V> acc{};
-#pragma unroll 8
-    for (int b = 0; b < B; ++b) {
-      const Bins<V> g = bins_load<V>(gY + ((long long)b * S + o) * P + p);
-      const Bins<V> x = bins_load<V>(X + ((long long)b * C + c) * P + p);
-#pragma unroll
-      for (int i = 0; i < V; ++i) acc.v[i] = cfmac(acc.v[i], g.v[i], x.v[i]);
-    }
-    bins_store<V>(gK + (long long)o * P + p, acc);
+    cic_sum<V, U>(acc, B, [&](int b) { return bins_load<V>(gY + ((long long)b * total + i)); },
+                  [&](int b) { return bins_load<V>(x + (long long)b * C * P); });
+    bins_store<V>(gK + i, acc);
   }
 }
 
@@ -2623,24 +2645,45 @@ hipError_t launch_cic_fwd(const float2 *X, const float2 *K, float2 *Y, int B, in
 
 hipError_t launch_cic_bwd_gx(const float2 *gY, const float2 *K, float2 *gX, int B, int C, int S, long long P,
                              hipStream_t s) {
-  return with_bins(bins_by_two(P, {gY, K, gX}), [&](auto vc) {
+  // Bins by twos, but one by one where 16-byte streams of planes far apart get less of the memory
+  // than 8-byte ones: one input channel of 2 or 3 outputs at 512 x 257 bins (32 images of 3: 34
+  // against 25 us), 4 or 5 outputs past 64 MB or at that size (32 images of 3 x 4 channels of 256 x
+  // 129: 37 against 33; but 16 of 8 x 2 17 against 25, 16 of 8 x 8 58 against 67).
+  const int J = S / C;
+  const bool far = P >= (1 << 17);
+  const bool one = J == 2 || J == 3 ? C == 1 && far : (J == 4 || J == 5) && (far || (long long)B * S * P >= (1 << 23));
+  return with_bins(!one && bins_by_two(P, {gY, K, gX}), [&](auto vc) {
     constexpr int V = decltype(vc)::value;
     int nt;
     dim3 grid = bins_grid(P, V, C, &nt);
     grid.z = (unsigned)std::min(B, 65535);
-    return timed_launch("cic_bwd_gx", k_cic_bwd_gx<V>, grid, dim3(nt), 0, s, gY, K, gX, B, C, S / C, P);
+    auto go = [&](auto kern) { return timed_launch("cic_bwd_gx", kern, grid, dim3(nt), 0, s, gY, K, gX, B, C, J, P); };
+    return (long long)B * C * P < (1 << 18) ? go(k_cic_bwd_gx<V, 4>) : go(k_cic_bwd_gx<V, 1>);
   });
 }
 
 hipError_t launch_cic_bwd_gk(const float2 *gY, const float2 *X, float2 *gK, int B, int C, int S, long long P,
                              hipStream_t s) {
-  // a thread's sum over the images is a chain of loads: few bins are shared out one by one
-  const bool two = (long long)S * P >= (1 << 18) && bins_by_two(P, {gY, X, gK});
+  // a thread's sum over the images is a chain of loads: few bins are shared out one by one, with
+  // the loads of four images issued together (32 images of 256 x 129 bins 5.0 us, by twos 6.7;
+  // of 512 x 257 bins 21 us, by twos 14)
+  const long long total = (long long)S * P;
+  const bool two = total >= (1 << 17) && bins_by_two(P, {gY, X, gK});
   return with_bins(two, [&](auto vc) {
     constexpr int V = decltype(vc)::value;
-    int nt;
-    const dim3 grid = bins_grid(P, V, S, &nt);
-    return timed_launch("cic_bwd_gk", k_cic_bwd_gk<V>, grid, dim3(nt), 0, s, gY, X, gK, B, C, S / C, P);
+    const unsigned grid = (unsigned)std::min<long long>((total / V + 255) / 256, 1 << 20);
+    auto go = [&](auto uc) {
+      constexpr int U = decltype(uc)::value;
+      if (total < (1LL << 31) - (1LL << 29) - 1024)  // the last step of the loop stays below 2^31
+        return timed_launch("cic_bwd_gk", k_cic_bwd_gk<V, U, int>, dim3(grid), dim3(256), 0, s, gY, X, gK, B, C, S / C,
+                            (int)P);
+      return timed_launch("cic_bwd_gk", k_cic_bwd_gk<V, U, long long>, dim3(grid), dim3(256), 0, s, gY, X, gK, B, C,
+                          S / C, P);
+    };
+    if constexpr (V == 1)
+      return go(std::integral_constant<int, 4>{});
+    else  // (16 images of 8 channels of 512 x 257 bins, J = 1: 46 us one by one, 42 by pairs of images)
+      return S == C && P >= (1 << 17) ? go(std::integral_constant<int, 2>{}) : go(std::integral_constant<int, 1>{});
   });
 }
 
