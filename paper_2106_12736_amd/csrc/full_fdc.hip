@@ -84,7 +84,8 @@ __host__ __device__ constexpr int tap_pad() {
 // Before (a row per image, bins singly): 16 images of 224^2, 64 -> 64 channels 225 -> 203 us;
 // 4 images of 512^2, 128 -> 128 channels 3.0 -> 1.68 ms; 3 images of 128^2, 48 -> 80 channels,
 // 5 x 5 taps 164 -> 64 us.  BT 8-image tiles share each K: BT = 1 with LB = 4 columns up to 8 images,
-// BT = 2 with LB = 2 beyond (the same 32 NTL accumulator registers: two waves a SIMD).
+// BT = 2 with LB = 2 beyond (the same 32 NTL accumulator registers: two waves a SIMD); BT = 1 with LB = 2
+// where the launch has too few workgroups for that to matter.
 // Every load is unconditional: images and channels past the end are clamped to the last
 // valid ones (their weights are zero, their outputs are not stored).
 // ---------------------------------------------------------------------------
@@ -182,12 +183,11 @@ __device__ __forceinline__ void kernel_pair(const float2 (&c)[NK], const float (
 
 // One workgroup's bins: main, row pair (k, P - k) and columns l0..l0 + LB - 1 of this wave;
 // SIDE, rows l0..l0 + LB - 1 <= P/2 and their negatives of the Nyquist column.
-template <int NK, int BT, int NTL, bool SIDE>
+template <int NK, int BT, int LB, int NTL, bool SIDE>
 __device__ __forceinline__ void contract_bins(const SpecLayout &in, const float *__restrict__ wt,
                                               const float2 *__restrict__ tw, const SpecLayout &out, float2 *cbuf,
                                               int B, int KD, int KDp, int ND, int NDp, int P, bool gx, int k, int l0,
                                               int b0, int n0) {
-  constexpr int LB = BT == 1 ? 4 : 2;
   const int H = P / 2;
   const int lane = threadIdx.x & 63, mrow = lane & 15, kk = lane >> 4;
   const bool valid = SIDE ? l0 <= H : l0 < H;  // this wave's bins (idle waves run along, storing nothing)
@@ -494,35 +494,59 @@ __device__ __forceinline__ void contract4_bins(const SpecLayout &in, const float
 
 // Workgroups per (output group, image tile): row pairs k = 0..P/2 times groups of 4 LB
 // columns, then the Nyquist column's groups of 4 LB rows 0..P/2.
-template <int BT>
-__host__ __device__ constexpr int ct_cols() {
-  return 4 * (BT == 1 ? 4 : 2);
-}
-static inline int ct_groups(int P, int cols) {
-  const int H = P / 2;
+static inline int ct_groups(int P, int lb) {
+  const int H = P / 2, cols = 4 * lb;
   return (H + 1) * ((H + cols - 1) / cols) + (H + cols) / cols;
 }
 
-template <int NK, int BT, int NTL>
+// Group g of them on one image tile and output group.
+template <int NK, int BT, int LB, int NTL>
+__device__ __forceinline__ void contract_group(const SpecLayout &in, const float *__restrict__ wt,
+                                               const float2 *__restrict__ tw, const SpecLayout &out, float2 *cbuf,
+                                               int B, int KD, int KDp, int ND, int NDp, int P, bool gx, int g, int b0,
+                                               int n0) {
+  constexpr int COLS = 4 * LB;
+  const int H = P / 2, ncg = (H + COLS - 1) / COLS;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (g < (H + 1) * ncg) {
+    const int k = g / ncg;
+    contract_bins<NK, BT, LB, NTL, false>(in, wt, tw, out, cbuf, B, KD, KDp, ND, NDp, P, gx, k,
+                                          (g - k * ncg) * COLS + wave * LB, b0, n0);
+  } else {
+    contract_bins<NK, BT, LB, NTL, true>(in, wt, tw, out, cbuf, B, KD, KDp, ND, NDp, P, gx, 0,
+                                         (g - (H + 1) * ncg) * COLS + wave * LB, b0, n0);
+  }
+}
+
+// Image tiles of 8 BT images from b_first on.
+template <int NK, int BT, int LB, int NTL>
 __global__ __launch_bounds__(256, 2) void k_full_contract(SpecLayout in, const float *__restrict__ wt,
                                                           const float2 *__restrict__ tw, SpecLayout out, int B, int KD,
                                                           int KDp, int ND, int NDp, int P, int gx, int ngroups,
                                                           int nsb, int b_first) {
   __shared__ float2 cbuf[ct_lds_elems<NK>()];
-  constexpr int COLS = ct_cols<BT>();
-  const int H = P / 2, ncg = (H + COLS - 1) / COLS;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int blk = xcd_remap(blockIdx.x, gridDim.x);
   const int sb = blk % nsb, rest = blk / nsb;
-  const int g = rest % ngroups, b0 = b_first + (rest / ngroups) * 8 * BT, n0 = sb * 16 * NTL;
-  if (g < (H + 1) * ncg) {
-    const int k = g / ncg;
-    contract_bins<NK, BT, NTL, false>(in, wt, tw, out, cbuf, B, KD, KDp, ND, NDp, P, gx != 0, k,
-                                      (g - k * ncg) * COLS + wave * (COLS / 4), b0, n0);
-  } else {
-    contract_bins<NK, BT, NTL, true>(in, wt, tw, out, cbuf, B, KD, KDp, ND, NDp, P, gx != 0, 0,
-                                     (g - (H + 1) * ncg) * COLS + wave * (COLS / 4), b0, n0);
-  }
+  contract_group<NK, BT, LB, NTL>(in, wt, tw, out, cbuf, B, KD, KDp, ND, NDp, P, gx != 0, rest % ngroups,
+                                  b_first + (rest / ngroups) * 8 * BT, sb * 16 * NTL);
+}
+
+// n16 tiles of 16 images and one of 8 for the rest: in a launch of their own the rest's
+// workgroups would wait for a last round of the others.
+template <int NK, int NTL>
+__global__ __launch_bounds__(256, 2) void k_full_contract_rest(SpecLayout in, const float *__restrict__ wt,
+                                                               const float2 *__restrict__ tw, SpecLayout out, int B,
+                                                               int KD, int KDp, int ND, int NDp, int P, int gx,
+                                                               int ng16, int n16, int nsb) {
+  __shared__ float2 cbuf[ct_lds_elems<NK>()];
+  const int blk = xcd_remap(blockIdx.x, gridDim.x);
+  const int sb = blk % nsb, rest = blk / nsb;
+  if (rest < ng16 * n16)
+    contract_group<NK, 2, 2, NTL>(in, wt, tw, out, cbuf, B, KD, KDp, ND, NDp, P, gx != 0, rest % ng16,
+                                  (rest / ng16) * 16, sb * 16 * NTL);
+  else
+    contract_group<NK, 1, 4, NTL>(in, wt, tw, out, cbuf, B, KD, KDp, ND, NDp, P, gx != 0, rest - ng16 * n16, 16 * n16,
+                                  sb * 16 * NTL);
 }
 
 // 4 images, 64 outputs a workgroup (grid as k_full_contract with BT = 1, one image tile).
@@ -532,7 +556,7 @@ __global__ __launch_bounds__(256, 3) void k_full_contract4(SpecLayout in, const 
                                                            int KD, int KDp, int ND, int NDp, int P, int gx, int nsb,
                                                            int b0) {
   __shared__ float2 cbuf[ct_lds_elems<NK>()];
-  constexpr int COLS = ct_cols<1>();
+  constexpr int COLS = 16;
   const int H = P / 2, ncg = (H + COLS - 1) / COLS;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int blk = xcd_remap(blockIdx.x, gridDim.x);
@@ -947,6 +971,9 @@ hipError_t launch_full_weights(const float *w, float *wt, bool gx, int S, int C,
                       gx ? 1 : 0, KDp, NDp);
 }
 
+// Workgroups of a launch: HIP counts threads in 32 bits.
+constexpr long long kCtMaxGrid = ((1LL << 32) - 1) / 256;
+
 hipError_t launch_full_contract(bool gx, int nk, SpecLayout in, const float *wt, const float2 *tw, SpecLayout out,
                                 int B, int KD, int ND, int P, hipStream_t s) {
   if (P % 8 != 0) return hipErrorInvalidValue;
@@ -956,60 +983,74 @@ hipError_t launch_full_contract(bool gx, int nk, SpecLayout in, const float *wt,
   const int tiles = (ND + 15) / 16, nsb = (tiles + 3) / 4;
   const char *nm = gx ? "full_contract_gx" : "full_contract_fwd";
   hipError_t err = hipErrorInvalidValue;
-  // 16-image tiles, and 8-image tiles for the last 8 or fewer images
+  // 16-image tiles, and an 8-image tile for the last 8 or fewer images
   const int n16 = (B + 7) / 8 / 2, rest = B - 16 * n16;
+  const int ng16 = ct_groups(P, 2), ng8 = ct_groups(P, 4);
   dispatch_nk(nk, [&](auto nc) {
     constexpr int NK = decltype(nc)::value;
-    auto go = [&](auto btc, auto ntc, int b_first, long long nbt) {
-      constexpr int BT = decltype(btc)::value, NTL = decltype(ntc)::value;
-      const int ng = ct_groups(P, ct_cols<BT>());
-      const long long per = (long long)ng * nsb, most = ((1LL << 31) - 1) / per;  // image tiles a launch can take
-      if (most < 1) {
-        err = hipErrorInvalidValue;
+    // `per` workgroups for each of `units` image tiles from b_first on, 8 BT images a tile; launches of
+    // at most kCtMaxGrid workgroups
+    auto go = [&](auto kern, int bt, long long per, int ng, int sbs, int b_first, long long units) {
+      const long long most = kCtMaxGrid / per;
+      err = most < 1 ? hipErrorInvalidValue : hipSuccess;
+      for (long long i = 0; i < units && err == hipSuccess; i += most)
+        err = timed_launch(nm, kern, dim3((unsigned)(per * std::min(most, units - i))), dim3(256), 0, s, in, wt, tw,
+                           out, B, KD, KDp, ND, NDp, P, gx ? 1 : 0, ng, sbs, (int)(b_first + i * 8 * bt));
+    };
+    // A launch of few workgroups, or of one or two steps, takes 8 images, 2 columns a wave and 32 or
+    // 16 outputs a workgroup: its time is a chain of steps, and these are the shortest.  3 x 3 taps:
+    // 64 -> 64 channels, 8 images of 32^2 16 us, 37 in the forms below, 20 images of 64^2 37 us, 66; 3 -> 64
+    // channels, 8 images of 224^2 38 us, 46 (but of 512^2, 5 x 5 taps, 4 images 117, 98).  Up to 512
+    // workgroups where half of a pair of tiles is idle (64^2, 9 images, 32 -> 48 channels, 548 workgroups:
+    // 19 us here, 17 below).
+    const int sbs = (tiles + 1) / 2;
+    const long long small = (long long)ng16 * sbs * ((B + 7) / 8);
+    const bool even = tiles % 2 == 0;
+    if (small <= (even ? 1024 : 512) || (KDp <= 8 && even && P < 512)) {
+      if (tiles == 1)
+        go(k_full_contract<NK, 1, 2, 1>, 1, ng16, ng16, 1, 0, (B + 7) / 8);
+      else
+        go(k_full_contract<NK, 1, 2, 2>, 1, (long long)ng16 * sbs, ng16, sbs, 0, (B + 7) / 8);
+      return;
+    }
+    auto with_ntl = [&](auto ntc) {
+      constexpr int NTL = decltype(ntc)::value;
+      const long long all = ((long long)ng16 * n16 + ng8) * nsb;
+      if (n16 > 0 && rest > 0 && all <= kCtMaxGrid) {
+        err = timed_launch(nm, k_full_contract_rest<NK, NTL>, dim3((unsigned)all), dim3(256), 0, s, in, wt, tw, out, B,
+                           KD, KDp, ND, NDp, P, gx ? 1 : 0, ng16, n16, nsb);
         return;
       }
-      for (long long i = 0; i < nbt; i += most) {
-        const long long n = std::min(most, nbt - i);
-        err = timed_launch(nm, k_full_contract<NK, BT, NTL>, dim3((unsigned)(per * n)), dim3(256), 0, s, in, wt, tw,
-                           out, B, KD, KDp, ND, NDp, P, gx ? 1 : 0, ng, nsb, (int)(b_first + i * 8 * BT));
-        if (err != hipSuccess) return;
-      }
-    };
-    auto with_ntl = [&](auto ntc) {
-      if (n16 > 0) go(std::integral_constant<int, 2>{}, ntc, 0, n16);
+      if (n16 > 0) go(k_full_contract<NK, 2, 2, NTL>, 2, (long long)ng16 * nsb, ng16, nsb, 0, n16);
       if (n16 > 0 && err != hipSuccess) return;
-      if (rest > 0) go(std::integral_constant<int, 1>{}, ntc, 16 * n16, 1);
+      if (rest > 0) go(k_full_contract<NK, 1, 4, NTL>, 1, (long long)ng8 * nsb, ng8, nsb, 16 * n16, 1);
     };
     // the last 1 to 4 images: 64 outputs a workgroup without idle rows, about 62 cycles for 64
     // kernel bins (3 x 3) where 8-image tiles take about 98, unless 16-output tiles waste less:
-    // up to 32 of 64 outputs at 3 x 3 taps, up to 48 at 5 x 5, where K takes more of both (48
-    // outputs of 128^2, 3 images: 68 us here, 65 on 8-image tiles; 128 -> 128 channels of
-    // 512^2, 4 images, 3 x 3: 1.12 ms here, 1.68 there)
-    if constexpr (NK == 3 || NK == 5) {
-      if (rest > 0 && rest <= 4 && (NK == 3 ? 2 * tiles >= 5 * nsb : 5 * tiles >= 16 * nsb)) {
-        if (n16 > 0) {
-          err = launch_full_contract(gx, nk, in, wt, tw, out, 16 * n16, KD, ND, P, s);
-          if (err != hipSuccess) return;
-        }
-        const long long grid = (long long)ct_groups(P, ct_cols<1>()) * nsb;
-        if (grid >= (1LL << 31)) {
-          err = hipErrorInvalidValue;
-          return;
-        }
-        err = timed_launch(nm, k_full_contract4<NK>, dim3((unsigned)grid), dim3(256), 0, s, in, wt, tw, out, B, KD,
-                           KDp, ND, NDp, P, gx ? 1 : 0, nsb, 16 * n16);
+    // up to 32 of 64 outputs up to 3 x 3 taps, up to 48 beyond, where K takes more of both (48
+    // outputs of 128^2, 3 images, 5 x 5: 68 us here, 65 on 8-image tiles; 128 -> 128 channels of
+    // 512^2, 4 images, 3 x 3: 1.12 ms here, 1.68 there; 256 -> 256 channels of 224^2, 4 images: 1 x 1 500 us
+    // here, 890 there, 2 x 2 745, 1110, 4 x 4 1023, 1340)
+    if (rest > 0 && rest <= 4 && (NK <= 3 ? 2 * tiles >= 5 * nsb : 5 * tiles >= 16 * nsb)) {
+      if (n16 > 0) {
+        err = launch_full_contract(gx, nk, in, wt, tw, out, 16 * n16, KD, ND, P, s);
+        if (err != hipSuccess) return;
+      }
+      const long long grid = (long long)ng8 * nsb;
+      if (grid > kCtMaxGrid) {
+        err = hipErrorInvalidValue;
         return;
       }
+      err = timed_launch(nm, k_full_contract4<NK>, dim3((unsigned)grid), dim3(256), 0, s, in, wt, tw, out, B, KD, KDp,
+                         ND, NDp, P, gx ? 1 : 0, nsb, 16 * n16);
+      return;
     }
-    if constexpr (NK == 3 || NK == 5) {
-      switch ((tiles + nsb - 1) / nsb) {
-        case 1: with_ntl(std::integral_constant<int, 1>{}); return;
-        case 2: with_ntl(std::integral_constant<int, 2>{}); return;
-        case 3: with_ntl(std::integral_constant<int, 3>{}); return;
-        default: break;
-      }
+    switch ((tiles + nsb - 1) / nsb) {
+      case 1: with_ntl(std::integral_constant<int, 1>{}); return;
+      case 2: with_ntl(std::integral_constant<int, 2>{}); return;
+      case 3: with_ntl(std::integral_constant<int, 3>{}); return;
+      default: with_ntl(std::integral_constant<int, 4>{});
     }
-    with_ntl(std::integral_constant<int, 4>{});
   });
   return err;
 }

@@ -125,6 +125,31 @@ def test_full_contraction_tiles(B, Cin, Cout, P, n):
     assert_parity(to_np(gw), gw_ref, "gw", rel=5e-6)
 
 
+# Sizes past the launches of few workgroups: images by 16, by 16 and the rest in one launch, by 8
+# and by 4, groups of one to four 16-output tiles and two of them, every kernel size; and few
+# channels of a large spectrum, which take the form of few workgroups.
+CONTRACT_LARGE_CASES = [
+    # B, Cin, Cout, P, n
+    (9, 17, 40, 64, 3),
+    (20, 40, 40, 64, 1),
+    (22, 40, 40, 64, 2),
+    (22, 12, 100, 64, 4),
+    (5, 40, 100, 128, 1),
+    (3, 20, 64, 128, 4),
+    (2, 20, 64, 128, 2),
+    (4, 20, 64, 128, 1),
+    (24, 18, 16, 128, 5),
+    (6, 12, 30, 224, 3),
+    (8, 3, 64, 128, 3),
+]
+
+
+@pytest.mark.parametrize("B,Cin,Cout,P,n", CONTRACT_LARGE_CASES)
+def test_full_contraction_large(B, Cin, Cout, P, n):
+    """As test_full_contraction_tiles, with sums over at most 100 channels."""
+    test_full_contraction_tiles(B, Cin, Cout, P, n)
+
+
 def test_full_layer_optional_outputs_and_repeatability():
     """Forward without `saved`, backward with only one of the two gradients, and
     bit-identical results on a second call (fixed reduction order)."""
