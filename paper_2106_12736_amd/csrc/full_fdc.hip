@@ -927,13 +927,22 @@ static bool dispatch_nk(int nk, F &&f) {
 
 bool full_kernel_size_supported(int nk) { return nk >= 1 && nk <= 5; }
 
-// Column ranges each row pair is cut into: about 1024 workgroups (four a compute unit) and
-// whole stages.
+// Column ranges each row pair is cut into: one workgroup is resident a compute unit (its LDS), so
+// the least of rounds x (stages + what a workgroup takes besides, 3 to 4 stages).  Against cutting
+// for 1024 workgroups, pass and reduction: 16 images of 224^2, 64 x 64 channels, 3 x 3 taps 207 -> 178 us;
+// 5 images of 128^2, 5 x 64 channels 50 -> 39; 2 images of 224^2, 33 x 16 64 -> 47.
 static int gw_ranges(int B, int S, int C, int P) {
-  const int lb = B <= 4 ? GwStage<4>::LB : GwStage<8>::LB, H = P / 2;
-  const long long tiles = (long long)((S + 31) / 32) * ((C + 31) / 32), wgs = tiles * (H + 2);
-  const long long ls = (1024 + wgs - 1) / wgs;
-  return (int)std::min<long long>(ls, (H + lb - 1) / lb);
+  const int lb = B <= 4 ? GwStage<4>::LB : GwStage<8>::LB, H = P / 2, nl = (H + lb - 1) / lb;
+  const int halves = B <= 4 ? 1 : (B + 7) / 8;
+  const long long wgs = (long long)((S + 31) / 32) * ((C + 31) / 32) * (H + 2);
+  int ranges = 1;
+  double least = 0.;
+  for (int ls = 1; ls <= nl; ++ls) {
+    const double rounds = (double)((wgs * ls + 255) / 256);
+    const double cost = rounds * ((nl + ls - 1) / ls * (double)halves + 2.5 + 0.5 * halves);
+    if (ls == 1 || cost < least) least = cost, ranges = ls;
+  }
+  return ranges;
 }
 // Floats of the dL/dw pass's partial sums.
 size_t full_gw_part_floats(int B, int S, int C, int P, int nk) {
