@@ -24,6 +24,7 @@
 // A[l % 16][l / 16], B[l / 16][l % 16] and D[4 (l / 16) + j][l % 16] in register j.
 #include "device.h"
 #include "internal.h"
+#include "launch_limit.h"
 #include "lds_limit.h"
 
 #include <hip/hip_runtime.h>
@@ -518,17 +519,17 @@ __device__ __forceinline__ void contract_group(const SpecLayout &in, const float
   }
 }
 
-// Image tiles of 8 BT images from b_first on.
+// Image tiles of 8 BT images from b_first on; workgroups from `first` on.
 template <int NK, int BT, int LB, int NTL>
 __global__ __launch_bounds__(256, 2) void k_full_contract(SpecLayout in, const float *__restrict__ wt,
                                                           const float2 *__restrict__ tw, SpecLayout out, int B, int KD,
                                                           int KDp, int ND, int NDp, int P, int gx, int ngroups,
-                                                          int nsb, int b_first) {
+                                                          int nsb, int b_first, unsigned first) {
   __shared__ float2 cbuf[ct_lds_elems<NK>()];
-  const int blk = xcd_remap(blockIdx.x, gridDim.x);
-  const int sb = blk % nsb, rest = blk / nsb;
+  const unsigned blk = first + xcd_remap(blockIdx.x, gridDim.x), rest = blk / nsb;
+  const int sb = blk % nsb;
   contract_group<NK, BT, LB, NTL>(in, wt, tw, out, cbuf, B, KD, KDp, ND, NDp, P, gx != 0, rest % ngroups,
-                                  b_first + (rest / ngroups) * 8 * BT, sb * 16 * NTL);
+                                  b_first + (int)(rest / ngroups) * 8 * BT, sb * 16 * NTL);
 }
 
 // n16 tiles of 16 images and one of 8 for the rest: in a launch of their own the rest's
@@ -537,11 +538,11 @@ template <int NK, int NTL>
 __global__ __launch_bounds__(256, 2) void k_full_contract_rest(SpecLayout in, const float *__restrict__ wt,
                                                                const float2 *__restrict__ tw, SpecLayout out, int B,
                                                                int KD, int KDp, int ND, int NDp, int P, int gx,
-                                                               int ng16, int n16, int nsb) {
+                                                               int ng16, int n16, int nsb, unsigned first) {
   __shared__ float2 cbuf[ct_lds_elems<NK>()];
-  const int blk = xcd_remap(blockIdx.x, gridDim.x);
-  const int sb = blk % nsb, rest = blk / nsb;
-  if (rest < ng16 * n16)
+  const unsigned blk = first + xcd_remap(blockIdx.x, gridDim.x), rest = blk / nsb;
+  const int sb = blk % nsb;
+  if (rest < (unsigned)(ng16 * n16))
     contract_group<NK, 2, 2, NTL>(in, wt, tw, out, cbuf, B, KD, KDp, ND, NDp, P, gx != 0, rest % ng16,
                                   (rest / ng16) * 16, sb * 16 * NTL);
   else
@@ -554,13 +555,13 @@ template <int NK>
 __global__ __launch_bounds__(256, 3) void k_full_contract4(SpecLayout in, const float *__restrict__ wt,
                                                            const float2 *__restrict__ tw, SpecLayout out, int B,
                                                            int KD, int KDp, int ND, int NDp, int P, int gx, int nsb,
-                                                           int b0) {
+                                                           int b0, unsigned first) {
   __shared__ float2 cbuf[ct_lds_elems<NK>()];
   constexpr int COLS = 16;
   const int H = P / 2, ncg = (H + COLS - 1) / COLS;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int blk = xcd_remap(blockIdx.x, gridDim.x);
-  const int g = blk / nsb, n0 = (blk - g * nsb) * kCtOut;
+  const unsigned blk = first + xcd_remap(blockIdx.x, gridDim.x);
+  const int g = blk / nsb, n0 = (int)(blk - g * nsb) * kCtOut;
   if (g < (H + 1) * ncg) {
     const int k = g / ncg;
     contract4_bins<NK, false>(in, wt, tw, out, cbuf, B, KD, KDp, ND, NDp, P, gx != 0, k,
@@ -815,15 +816,16 @@ __device__ __forceinline__ void gw_rows(const SpecLayout &G, const SpecLayout &X
   }
 }
 
-// Chunks: row pairs k = 0..P/2, then the Nyquist column, each in `ls` column ranges.
+// Chunks: row pairs k = 0..P/2, then the Nyquist column, each in `ls` column ranges; workgroups
+// from `first` on.
 template <int NK, int IMG, bool GAUSS>
 __global__ __launch_bounds__(kGwThreads) void k_full_gw(SpecLayout G, SpecLayout X, const float2 *__restrict__ tw,
                                                         float *__restrict__ part, int B, int S, int C, int P,
-                                                        int ls) {
+                                                        int ls, unsigned first) {
   extern __shared__ float2 gw_lds[];
   const int H = P / 2;
   const int cblocks = (C + 31) / 32, tiles = ((S + 31) / 32) * cblocks;
-  const int blk = xcd_remap(blockIdx.x, gridDim.x);
+  const int blk = (int)first + xcd_remap(blockIdx.x, gridDim.x);
   const int chunk = blk / tiles, tile = blk - chunk * tiles;
   const int k = chunk / ls, range = chunk - k * ls;
   // whole stages a range
@@ -845,12 +847,13 @@ __global__ __launch_bounds__(kGwThreads) void k_full_gw(SpecLayout G, SpecLayout
 // 224^2, 64 x 64 channels 14.3 -> 16.1 us, 4 of 128^2, 128 x 128, 5 x 5 taps 14.0 -> 18.4 us.
 template <int NK, int PP>
 __global__ __launch_bounds__(256) void k_full_gw_reduce(const float *__restrict__ part, const float2 *__restrict__ tw,
-                                                        float *__restrict__ gw, long long pairs, int P, int ls) {
+                                                        float *__restrict__ gw, long long pairs, int P, int ls,
+                                                        unsigned first) {
   constexpr int T = NK * NK, R = gw_record(NK);
   constexpr int GR = 256 / PP;
   __shared__ double red[GR][PP][T + 1];
   const int H = P / 2, o = threadIdx.x % PP, w = threadIdx.x / PP, chunks = (H + 2) * ls;
-  const long long i = (long long)blockIdx.x * PP + o, ii = i < pairs ? i : pairs - 1;
+  const long long base = ((long long)first + blockIdx.x) * PP, i = base + o, ii = i < pairs ? i : pairs - 1;
   double acc[T];
 #pragma unroll
   for (int t = 0; t < T; ++t) acc[t] = 0.;
@@ -883,11 +886,11 @@ __global__ __launch_bounds__(256) void k_full_gw_reduce(const float *__restrict_
   __syncthreads();
   for (int e = threadIdx.x; e < PP * T; e += 256) {
     const int oo = e / T, t = e - oo * T;
-    if ((long long)blockIdx.x * PP + oo >= pairs) break;
+    if (base + oo >= pairs) break;
     double s = red[0][oo][t];
 #pragma unroll
     for (int q = 1; q < GR; ++q) s += red[q][oo][t];
-    gw[((long long)blockIdx.x * PP + oo) * T + t] = (float)s;
+    gw[(base + oo) * T + t] = (float)s;
   }
 }
 
@@ -944,19 +947,21 @@ static int gw_ranges(int B, int S, int C, int P) {
   }
   return ranges;
 }
+
 // Floats of the dL/dw pass's partial sums.
 size_t full_gw_part_floats(int B, int S, int C, int P, int nk) {
   return (size_t)(P / 2 + 2) * gw_ranges(B, S, C, P) * S * C * gw_record(nk);
 }
 
+// Sizes a plan accepts: below 2^31 contraction tiles (4 runs of 4 bins, 64 outputs, 16 images), dL/dw
+// workgroups and workgroups of its reduction.  Launches of any size in these limits run (in_launches).
 bool full_launch_fits(int B, int Cin, int Cout, int P, int nk) {
   if (P % 8 != 0 || B < 1 || B > 65535 * 16) return false;
   const long long nrun = (long long)P * (P / 2) / 4 + P / 4;
-  const long long nwg_run = (nrun + 3) / 4, nbt = (B + 15) / 16;
+  const long long nrun4 = (nrun + 3) / 4, nbt = (B + 15) / 16;
   const long long lim = 1LL << 31;
-  // the two contractions
-  if (nwg_run * ((Cout + kCtOut - 1) / kCtOut) * nbt >= lim) return false;
-  if (nwg_run * ((Cin + kCtOut - 1) / kCtOut) * nbt >= lim) return false;
+  if (nrun4 * ((Cout + kCtOut - 1) / kCtOut) * nbt >= lim) return false;
+  if (nrun4 * ((Cin + kCtOut - 1) / kCtOut) * nbt >= lim) return false;
   // dL/dw: tiles of 32 x 32 (s, c) times bin chunks, and the fixed-order reduction
   const long long tiles = (long long)((Cout + 31) / 32) * ((Cin + 31) / 32);
   if (tiles * (P / 2 + 2) * gw_ranges(B, Cout, Cin, P) >= lim) return false;
@@ -980,9 +985,6 @@ hipError_t launch_full_weights(const float *w, float *wt, bool gx, int S, int C,
                       gx ? 1 : 0, KDp, NDp);
 }
 
-// Workgroups of a launch: HIP counts threads in 32 bits.
-constexpr long long kCtMaxGrid = ((1LL << 32) - 1) / 256;
-
 hipError_t launch_full_contract(bool gx, int nk, SpecLayout in, const float *wt, const float2 *tw, SpecLayout out,
                                 int B, int KD, int ND, int P, hipStream_t s) {
   if (P % 8 != 0) return hipErrorInvalidValue;
@@ -997,14 +999,12 @@ hipError_t launch_full_contract(bool gx, int nk, SpecLayout in, const float *wt,
   const int ng16 = ct_groups(P, 2), ng8 = ct_groups(P, 4);
   dispatch_nk(nk, [&](auto nc) {
     constexpr int NK = decltype(nc)::value;
-    // `per` workgroups for each of `units` image tiles from b_first on, 8 BT images a tile; launches of
-    // at most kCtMaxGrid workgroups
-    auto go = [&](auto kern, int bt, long long per, int ng, int sbs, int b_first, long long units) {
-      const long long most = kCtMaxGrid / per;
-      err = most < 1 ? hipErrorInvalidValue : hipSuccess;
-      for (long long i = 0; i < units && err == hipSuccess; i += most)
-        err = timed_launch(nm, kern, dim3((unsigned)(per * std::min(most, units - i))), dim3(256), 0, s, in, wt, tw,
-                           out, B, KD, KDp, ND, NDp, P, gx ? 1 : 0, ng, sbs, (int)(b_first + i * 8 * bt));
+    // ng x sbs workgroups for each of `units` image tiles from b_first on
+    auto go = [&](auto kern, int ng, int sbs, int b_first, long long units) {
+      err = in_launches((long long)ng * sbs * units, 256, hipSuccess, [&](unsigned n, unsigned first) {
+        return timed_launch(nm, kern, dim3(n), dim3(256), 0, s, in, wt, tw, out, B, KD, KDp, ND, NDp, P, gx ? 1 : 0,
+                            ng, sbs, b_first, first);
+      });
     };
     // A launch of few workgroups, or of one or two steps, takes 8 images, 2 columns a wave and 32 or
     // 16 outputs a workgroup: its time is a chain of steps, and these are the shortest.  3 x 3 taps:
@@ -1015,24 +1015,24 @@ hipError_t launch_full_contract(bool gx, int nk, SpecLayout in, const float *wt,
     const int sbs = (tiles + 1) / 2;
     const long long small = (long long)ng16 * sbs * ((B + 7) / 8);
     const bool even = tiles % 2 == 0;
-    if (small <= (even ? 1024 : 512) || (KDp <= 8 && even && P < 512)) {
+    if (small <= (even ? 1024 : 512) || (KDp <= 8 && even && P < 512 && small < (1LL << 31))) {
       if (tiles == 1)
-        go(k_full_contract<NK, 1, 2, 1>, 1, ng16, ng16, 1, 0, (B + 7) / 8);
+        go(k_full_contract<NK, 1, 2, 1>, ng16, 1, 0, (B + 7) / 8);
       else
-        go(k_full_contract<NK, 1, 2, 2>, 1, (long long)ng16 * sbs, ng16, sbs, 0, (B + 7) / 8);
+        go(k_full_contract<NK, 1, 2, 2>, ng16, sbs, 0, (B + 7) / 8);
       return;
     }
     auto with_ntl = [&](auto ntc) {
       constexpr int NTL = decltype(ntc)::value;
-      const long long all = ((long long)ng16 * n16 + ng8) * nsb;
-      if (n16 > 0 && rest > 0 && all <= kCtMaxGrid) {
-        err = timed_launch(nm, k_full_contract_rest<NK, NTL>, dim3((unsigned)all), dim3(256), 0, s, in, wt, tw, out, B,
-                           KD, KDp, ND, NDp, P, gx ? 1 : 0, ng16, n16, nsb);
-        return;
-      }
-      if (n16 > 0) go(k_full_contract<NK, 2, 2, NTL>, 2, (long long)ng16 * nsb, ng16, nsb, 0, n16);
-      if (n16 > 0 && err != hipSuccess) return;
-      if (rest > 0) go(k_full_contract<NK, 1, 4, NTL>, 1, (long long)ng8 * nsb, ng8, nsb, 16 * n16, 1);
+      if (n16 > 0 && rest > 0)
+        err = in_launches(((long long)ng16 * n16 + ng8) * nsb, 256, hipSuccess, [&](unsigned n, unsigned first) {
+          return timed_launch(nm, k_full_contract_rest<NK, NTL>, dim3(n), dim3(256), 0, s, in, wt, tw, out, B, KD, KDp,
+                              ND, NDp, P, gx ? 1 : 0, ng16, n16, nsb, first);
+        });
+      else if (n16 > 0)
+        go(k_full_contract<NK, 2, 2, NTL>, ng16, nsb, 0, n16);
+      else
+        go(k_full_contract<NK, 1, 4, NTL>, ng8, nsb, 0, 1);
     };
     // the last 1 to 4 images: 64 outputs a workgroup without idle rows, about 62 cycles for 64
     // kernel bins (3 x 3) where 8-image tiles take about 98, unless 16-output tiles waste less:
@@ -1045,13 +1045,10 @@ hipError_t launch_full_contract(bool gx, int nk, SpecLayout in, const float *wt,
         err = launch_full_contract(gx, nk, in, wt, tw, out, 16 * n16, KD, ND, P, s);
         if (err != hipSuccess) return;
       }
-      const long long grid = (long long)ng8 * nsb;
-      if (grid > kCtMaxGrid) {
-        err = hipErrorInvalidValue;
-        return;
-      }
-      err = timed_launch(nm, k_full_contract4<NK>, dim3((unsigned)grid), dim3(256), 0, s, in, wt, tw, out, B, KD, KDp,
-                         ND, NDp, P, gx ? 1 : 0, nsb, 16 * n16);
+      err = in_launches((long long)ng8 * nsb, 256, hipSuccess, [&](unsigned n, unsigned first) {
+        return timed_launch(nm, k_full_contract4<NK>, dim3(n), dim3(256), 0, s, in, wt, tw, out, B, KD, KDp, ND, NDp,
+                            P, gx ? 1 : 0, nsb, 16 * n16, first);
+      });
       return;
     }
     switch ((tiles + nsb - 1) / nsb) {
@@ -1085,18 +1082,20 @@ hipError_t launch_full_gw(int nk, SpecLayout G, SpecLayout X, const float2 *tw, 
       static_assert(lds <= 160 * 1024 && lds >= (size_t)3 * 256 * 8 * NK * sizeof(float), "dL/dw: LDS");
       err = allow_lds<k_full_gw<NK, IMG, kGauss>>(lds);
       if (err != hipSuccess) return;
-      err = timed_launch("full_gw", k_full_gw<NK, IMG, kGauss>, dim3((unsigned)grid), dim3(kGwThreads), lds, s, G, X,
-                         tw, part, B, S, C, P, ls);
+      err = in_launches(grid, kGwThreads, hipSuccess, [&](unsigned n, unsigned first) {
+        return timed_launch("full_gw", k_full_gw<NK, IMG, kGauss>, dim3(n), dim3(kGwThreads), lds, s, G, X, tw, part,
+                            B, S, C, P, ls, first);
+      });
     };
     if (B <= 4)
       go(std::integral_constant<int, 4>{});
     else
       go(std::integral_constant<int, 8>{});
     if (err != hipSuccess) return;
-    err = pp == 8 ? timed_launch("full_gw_reduce", k_full_gw_reduce<NK, 8>, dim3((unsigned)rgrid), dim3(256), 0, s,
-                                 part, tw, gw, pairs, P, ls)
-                  : timed_launch("full_gw_reduce", k_full_gw_reduce<NK, 32>, dim3((unsigned)rgrid), dim3(256), 0, s,
-                                 part, tw, gw, pairs, P, ls);
+    err = in_launches(rgrid, 256, hipSuccess, [&](unsigned n, unsigned first) {
+      return timed_launch("full_gw_reduce", pp == 8 ? k_full_gw_reduce<NK, 8> : k_full_gw_reduce<NK, 32>, dim3(n),
+                          dim3(256), 0, s, part, tw, gw, pairs, P, ls, first);
+    });
   });
   return err;
 }

@@ -8,6 +8,7 @@
 #include <cstdint>
 
 #include "fdc.h"
+#include "launch_limit.h"
 
 namespace fdc {
 
@@ -101,6 +102,8 @@ bool timing_slot(const char *name, hipEvent_t *start, hipEvent_t *stop);
 template <class Kern, class... Args>
 inline hipError_t timed_launch(const char *name, Kern kern, dim3 grid, dim3 block, size_t lds, hipStream_t s,
                                Args... args) {
+  if (!launch_counts(grid.x, block.x) || !launch_counts(grid.y, block.y) || !launch_counts(grid.z, block.z))
+    return hipErrorInvalidConfiguration;
   hipEvent_t e0, e1;
   if (timing_slot(name, &e0, &e1))
     hipExtLaunchKernelGGL(kern, grid, block, (std::uint32_t)lds, s, e0, e1, 0u, args...);

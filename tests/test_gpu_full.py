@@ -150,6 +150,32 @@ def test_full_contraction_large(B, Cin, Cout, P, n):
     test_full_contraction_tiles(B, Cin, Cout, P, n)
 
 
+def test_full_weight_gradient_large_grid():
+    """dL/dw of 4096 x 4096 channels: 16384 tiles x 258 bin chunks = 4.2 million workgroups of 1024
+    threads, more than the 2^32 threads that HIP counts in a launch; a launch cut short leaves the last
+    chunks out of every sum.  A 1 x 1 kernel scales, so dL/dw[s, c] = <gy_s, x_c>, in 64 bits for 48
+    pairs in either direction.  Bound as in test_full_contraction_tiles."""
+    S = C = 4096
+    P = 512
+    if torch.cuda.mem_get_info()[0] < 64 << 30:
+        pytest.skip("64 GiB of device memory are needed")
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    x = torch.randn(1, C, P, P, device="cuda", generator=gen)
+    w = torch.randn(S, C, 1, 1, device="cuda", generator=gen)
+    layer = layers.FullLayer(1, C, S, P, kernel_n=1, artifact="none")
+    saved = layer.new_saved()
+    y = layer.forward(x, w, saved=saved)
+    rows, cols = torch.arange(0, S, 87, device="cuda"), torch.arange(C - 1, -1, -87, device="cuda")
+    ref = w[rows, :, 0, 0].double() @ x[0, :, 5].double()
+    got = y[0, rows, 5].double()
+    assert float((got - ref).abs().max() / ref.abs().max()) < 5e-6
+    del y, got, ref
+    gy = torch.randn(1, S, P, P, device="cuda", generator=gen)
+    _, gw = layer.backward(gy, saved, None, need_gx=False)
+    ref = gy[0, rows].double().flatten(1) @ x[0, cols].double().flatten(1).t()
+    assert float((gw[rows][:, cols, 0, 0].double() - ref).abs().max() / ref.abs().max()) < 5e-6
+
+
 def test_full_layer_optional_outputs_and_repeatability():
     """Forward without `saved`, backward with only one of the two gradients, and
     bit-identical results on a second call (fixed reduction order)."""
