@@ -28,6 +28,8 @@ of the same workload.
 """
 
 import argparse
+import ctypes
+import functools
 import hashlib
 import json
 import os
@@ -80,25 +82,24 @@ def gk_launches(B, C, S, N, M, L, NF, ranges=1, zeros=True):
             ("gk_reduce", C64 * (R * S * M * L + gk_bytes))]
 
 
-def small_layer(N, M):
-    """Whether a layer call runs its forward (and most backwards) in one launch."""
-    return (N, M) in ((32, 32), (32, 16), (32, 8), (64, 64), (64, 32), (64, 16), (128, 64), (128, 32))
+@functools.lru_cache(maxsize=None)
+def one_launch(B, C, S, N, M):
+    """(forward, backward) of fdc_cic_layer_one_launch for a layer of these sizes."""
+    from paper_2106_12736_amd import _lib
 
-
-def small_backward(B, C, S, N, M):
-    """The rule of small_bwd_supported (csrc/small.hip)."""
-    J, planes = S // C, B * C
-    if not small_layer(N, M):
-        return False
-    if M == 64:
-        return J == 1 or (J == 2 and (N == 64 or planes < 512)) or (J <= 4 and N == 64 and planes < 512)
-    return not (M == 32 and N <= 64 and J >= 4 and planes >= 1024)
+    plan, fwd, bwd = ctypes.c_void_p(), ctypes.c_int(), ctypes.c_int()
+    _lib.call("fdc_cic_layer_plan_create", ctypes.byref(plan), B, C, S, N, M, 0, 1)
+    try:
+        _lib.call("fdc_cic_layer_one_launch", plan, ctypes.byref(fwd), ctypes.byref(bwd))
+    finally:
+        _lib.call("fdc_layer_plan_destroy", plan)
+    return fwd.value, bwd.value
 
 
 def layer_fwd_launches(B, C, S, N, M, L, out):
     """A layer call's forward from images B x C x N x N to B x S x out x out."""
     x, y = F32 * B * C * N * N, F32 * B * S * out * out
-    if small_layer(N, M):
+    if one_launch(B, C, S, N, M)[0]:
         return [(f"small_fwd_{N}_{M}", x + C64 * (S * M * L + B * C * M * L) + y)]
     return [(f"row_r2c_{N}", x + C64 * B * C * N * L), *fwd_col_launches(B, C, S, N, M, L),
             (f"row_c2r_{M}", C64 * B * S * M * L + y)]
@@ -107,11 +108,11 @@ def layer_fwd_launches(B, C, S, N, M, L, out):
 def layer_bwd_launches(B, C, S, N, M, L, NF, out, ranges=1, dx=True):
     """A layer call's backward: gK, and gx with dx."""
     gy, gx = F32 * B * S * out * out, F32 * B * C * N * N
-    if small_backward(B, C, S, N, M):
-        R = ranges
-        gk = R * S * M * L if R > 1 else S * N * NF
+    small = one_launch(B, C, S, N, M)[1]
+    if small:
+        gk = ranges * S * M * L if small == 2 else S * N * NF
         one = (f"small_bwd_{N}_{M}", gy + C64 * (B * C * M * L + gk) + (C64 * S * M * L + gx if dx else 0))
-        return [one] + ([("gk_reduce", C64 * (R * S * M * L + S * N * NF))] if R > 1 else [])
+        return [one] + ([("gk_reduce", C64 * (ranges * S * M * L + S * N * NF))] if small == 2 else [])
     res = [(f"row_r2c_{M}", gy + C64 * B * S * M * L), *gk_launches(B, C, S, N, M, L, NF, ranges)]
     if dx:
         res.append((f"col_bwd_gx_{N}_{M}", C64 * (B * S * M * L + S * M * L + B * C * N * L)))

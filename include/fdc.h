@@ -428,11 +428,17 @@ fdc_status fdc_kernel_timing_launches(char *buf, size_t buf_bytes);
  * adds the ranges in range order and writes gK, so results stay repeatable.  R
  * depends only on the plan: larger batches are cut into ranges so that enough
  * workgroups run at once.  A layer plan whose whole backward is one launch
- * ("small_bwd_<N>_<M>", N <= 128) sums R ranges in it and adds them the same way.
+ * ("small_bwd_<N>_<M>", see fdc_cic_layer_one_launch) sums R ranges in it and adds them
+ * the same way; with R = 1 it may still leave gK to the second launch.
  * Layer plans of the spectral-kernel CIC layer (the plan's layer for the stack call);
  * FDC_EINVAL for other plans or layers. */
 fdc_status fdc_cic_layer_dk_ranges(const fdc_layer_plan *plan, int *ranges);
 fdc_status fdc_cic_stack_dk_ranges(const fdc_stack_plan *plan, int layer, int *ranges);
+/* Whether a layer plan's calls run in one launch (measurement support).  *forward: 1 when
+ * the forward is one ("small_fwd_<N>_<M>"), 0 for separate launches.  *backward: 0 for
+ * separate launches, 1 when the backward is one launch ("small_bwd_<N>_<M>"), 2 when
+ * "gk_reduce" follows it.  Both depend only on the plan. */
+fdc_status fdc_cic_layer_one_launch(const fdc_layer_plan *plan, int *forward, int *backward);
 /* The first layer of the stack's LDS-resident tail (the last two layers run by
  * "tail_fwd_<N>_<M1>_<M2>", "tail_bwd_<N>_<M1>_<M2>" and one "gk_reduce" launch),
  * or -1 when every layer runs on the per-layer kernels.  The dK ranges query does

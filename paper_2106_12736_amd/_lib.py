@@ -82,6 +82,7 @@ _SIGS = {
     "fdc_kernel_timing_report": [ctypes.c_char_p, _SZ],
     "fdc_kernel_timing_launches": [ctypes.c_char_p, _SZ],
     "fdc_cic_layer_dk_ranges": [_P, ctypes.POINTER(_I)],
+    "fdc_cic_layer_one_launch": [_P, ctypes.POINTER(_I), ctypes.POINTER(_I)],
     "fdc_cic_stack_dk_ranges": [_P, _I, ctypes.POINTER(_I)],
     "fdc_cic_stack_tail": [_P, ctypes.POINTER(_I)],
 }

@@ -1309,6 +1309,16 @@ fdc_status fdc_cic_layer_dk_ranges(const fdc_layer_plan *p, int *ranges) {
   return FDC_OK;
 }
 
+fdc_status fdc_cic_layer_one_launch(const fdc_layer_plan *p, int *forward, int *backward) {
+  if (fdc_status st = check_layer_plan(p, 0)) return st;
+  if (forward == nullptr || backward == nullptr) return fail(FDC_EINVAL, "forward or backward is NULL");
+  *forward = fdc::small_fwd_supported(p->N, p->M, p->B, p->C, p->S);
+  *backward = !fdc::small_bwd_supported(p->N, p->M, p->B, p->C, p->S) ? 0
+              : fdc::small_bwd_parts(p->N, p->M, p->B, p->C, p->S)    ? 2
+                                                                      : 1;
+  return FDC_OK;
+}
+
 fdc_status fdc_cic_stack_tail(const fdc_stack_plan *p, int *first_layer) {
   if (fdc_status st = check_stack_plan(p)) return st;
   if (first_layer == nullptr) return fail(FDC_EINVAL, "first_layer is NULL");

@@ -209,6 +209,7 @@ bool small_layer_supported(int n, int m);
 bool small_fwd_supported(int n, int m, int B, int C, int S);
 bool small_bwd_supported(int n, int m, int B, int C, int S);
 int small_bwd_ranges(int n, int m, int B, int C, int S);
+bool small_bwd_parts(int n, int m, int B, int C, int S);  // gK is left to launch_gk_reduce2
 hipError_t launch_small_fwd(int n, int m, const float *x, const float2 *K, SpecLayout saved, float *y, ImgView view,
                             long long out_plane, int B, int C, int S, hipStream_t s);
 hipError_t launch_small_bwd(int n, int m, const float *gy, ImgView view, long long out_plane, SpecLayout saved,

@@ -628,6 +628,7 @@ hipError_t launch_small_fwd(int n, int m, const float *x, const float2 *K, SpecL
 }
 
 int small_bwd_ranges(int n, int m, int B, int C, int S) { return small_plan(n, m, B, C, S / C).R; }
+bool small_bwd_parts(int n, int m, int B, int C, int S) { return small_plan(n, m, B, C, S / C).parts != 0; }
 
 hipError_t launch_small_bwd(int n, int m, const float *gy, ImgView view, long long out_plane, SpecLayout saved,
                             const float2 *K, float *gx, float2 *gK, float2 *part, int B, int C, int S,

@@ -190,6 +190,13 @@ class CicLayer(_LayerPlan):
         call("fdc_cic_layer_dk_ranges", self._p, ctypes.byref(r))
         return r.value
 
+    def one_launch(self):
+        """(forward, backward): whether each call is one launch; backward 2: and gk_reduce
+        (fdc_cic_layer_one_launch)."""
+        f, b = ctypes.c_int(), ctypes.c_int()
+        call("fdc_cic_layer_one_launch", self._p, ctypes.byref(f), ctypes.byref(b))
+        return f.value, b.value
+
     def saved_spectrum(self, saved):
         """The M x (M/2+1) kept bins held in a saved buffer, as a [B][C][M][M/2+1] tensor:
         columns 0..M/2-1 come from the main block (8-column tiles [M/16][M][8] per

@@ -390,6 +390,25 @@ def test_small_layer_backward_route(N, M, B, C, J, most):
     assert 1 <= r.value <= most
 
 
+@pytest.mark.parametrize("N,M,B,C,J,forward,backward", [
+    (64, 32, 4, 64, 4, 1, 2),    # the planes' zeros go to the sum's launch
+    (64, 64, 1, 4, 4, 1, 1),
+    (64, 16, 16, 65, 5, 1, 0),
+    (128, 64, 16, 20, 2, 0, 0),
+    (32, 32, 128, 3, 1, 1, 2),
+    (256, 128, 4, 4, 2, 0, 0),   # not a small layer
+])
+def test_layer_one_launch_query(N, M, B, C, J, forward, backward):
+    f, b, lp = ctypes.c_int(), ctypes.c_int(), ctypes.c_void_p()
+    assert _lib.status("fdc_cic_layer_plan_create", ctypes.byref(lp), B, C, C * J, N, M, 0, 1) == FDC_OK
+    assert _lib.status("fdc_cic_layer_one_launch", lp, ctypes.byref(f), ctypes.byref(b)) == FDC_OK
+    assert (f.value, b.value) == (forward, backward)
+    assert _lib.status("fdc_cic_layer_one_launch", lp, None, ctypes.byref(b)) == FDC_EINVAL
+    assert _lib.status("fdc_cic_layer_one_launch", lp, ctypes.byref(f), None) == FDC_EINVAL
+    assert _lib.status("fdc_layer_plan_destroy", lp) == FDC_OK
+    assert _lib.status("fdc_cic_layer_one_launch", lp, ctypes.byref(f), ctypes.byref(b)) == FDC_EINVAL  # destroyed
+
+
 def test_head_and_adam_validation():
     """The classifier head and Adam refuse bad sizes and NULL arguments on the host,
     before any launch; the head workspace is one float per (chunk of 1024 features,

@@ -5,6 +5,7 @@ The stack tests run the four synthetic CIC workloads at their full sizes, in
 the same launch configuration the benchmark times (paper_2106_12736_amd.layers.CicStack),
 and compare every output and every gradient element."""
 
+import ctypes
 import zlib
 
 import numpy as np
@@ -13,7 +14,7 @@ import torch
 
 from _parity import assert_parity, to_np
 from oracle import fdc
-from paper_2106_12736_amd import inputs, layers
+from paper_2106_12736_amd import _lib, inputs, layers
 
 pytestmark = pytest.mark.gpu
 
@@ -221,6 +222,34 @@ def test_stack_full_size(wl):
     gks2 = [g.clone() for g in stack.backward(_gpu(d.grad), Ks)]
     for a, b in zip(gks2, gks):
         assert torch.equal(a, b)
+
+
+def _launch_names(f):
+    buf = ctypes.create_string_buffer(1 << 14)
+    _lib.call("fdc_kernel_timing_enable", 16, None)
+    try:
+        f()
+        torch.cuda.synchronize()
+        _lib.call("fdc_kernel_timing_launches", buf, len(buf))
+    finally:
+        _lib.call("fdc_kernel_timing_disable")
+    return [line.split()[0] for line in buf.value.decode().splitlines()]
+
+
+@pytest.mark.parametrize("N,M,B,C,J", [(64, 32, 4, 64, 4), (64, 64, 1, 4, 4), (64, 16, 16, 65, 5), (128, 64, 16, 20, 2),
+                                       (128, 32, 1, 20, 2)])
+def test_one_launch_query_names_the_launches(N, M, B, C, J):
+    """fdc_cic_layer_one_launch against the launches that the two calls make."""
+    layer = layers.CicLayer(B, C, C * J, N, M, "none", 1)
+    x, gy = torch.zeros(B, C, N, N, device="cuda"), torch.zeros(B, C * J, M, M, device="cuda")
+    K = torch.zeros(C * J, N, N // 2 + 1, dtype=torch.complex64, device="cuda")
+    saved = layer.new_saved()
+    fwd = _launch_names(lambda: layer.forward(x, K, saved=saved))
+    bwd = _launch_names(lambda: layer.backward(gy, saved, K))
+    forward, backward = layer.one_launch()
+    assert (fwd == [f"small_fwd_{N}_{M}"]) == (forward == 1), fwd
+    assert (bwd == [f"small_bwd_{N}_{M}"]) == (backward == 1), bwd
+    assert (bwd == [f"small_bwd_{N}_{M}", "gk_reduce"]) == (backward == 2), bwd
 
 
 # Forms that the number of planes decides: several images a workgroup with an uneven last range

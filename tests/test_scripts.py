@@ -52,6 +52,21 @@ def test_pooled_rfft2_work_model(n, m):
         assert sum(b for _, b in got) < sum(b for _, b in full)
 
 
+@pytest.mark.parametrize("B,C,S,N,M,fwd,bwd", [
+    (4, 64, 256, 64, 32, ["small_fwd_64_32"], ["small_bwd_64_32", "gk_reduce"]),
+    (1, 4, 16, 64, 64, ["small_fwd_64_64"], ["small_bwd_64_64"]),
+    (16, 20, 40, 128, 64, ["row_r2c_128", "col_fwd_cic_128_64", "row_c2r_64"],
+     ["row_r2c_64", "col_bwd_gk_64", "col_bwd_gx_128_64", "row_c2r_128"]),
+])
+def test_layer_work_model_follows_the_library(B, C, S, N, M, fwd, bwd):
+    """The launches counted for a layer call are the ones the library chooses for it: several
+    workgroup rounds of the one-launch kernels go to separate launches, and one image range
+    may still be summed by a second launch."""
+    L, NF = M // 2 + 1, N // 2 + 1
+    assert [nm for nm, _ in bench.layer_fwd_launches(B, C, S, N, M, L, M)] == fwd
+    assert [nm for nm, _ in bench.layer_bwd_launches(B, C, S, N, M, L, NF, M)] == bwd
+
+
 def test_chain_work_model_starts_with_the_pooled_transform():
     wl = inputs.STACK1024
     launches = bench.chain_step_launches(wl)
