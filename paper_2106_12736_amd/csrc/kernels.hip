@@ -2410,7 +2410,10 @@ constexpr int kWgradStackRows = 64;
 // Re sum_l conj(W^(l b)) F_a(l) with F_a(l) = sum_k dK(k, l) conj(W^(k a)) (k the
 // N-grid row of a kept row): a lane owns one column l and sums F_a(l) down the
 // workgroup's rows (a wave reads a row segment of 64 bins with one load), projects it
-// onto the taps at the end, and the workgroup adds its 256 lanes in a fixed order.
+// onto the taps at the end, and the workgroup adds its 256 lanes in a fixed order.  Rows are
+// summed by fours: one chain of 16 made the error of dL/dw 6 % larger than cross-lane sums of every
+// row have it (64 x 64, 3 x 3 taps: 2.31e-7 of which 1.9e-7 are the transforms', now 2.21e-7; a
+// backward call takes the same time within 1 us).
 // Workgroup (layer, o, column block cb, row block rb) writes
 // part[(o * ncb * rowb + cb * rowb + rb) * NK^2 + tap] of its layer.
 template <int NK>
@@ -2443,6 +2446,9 @@ __global__ __launch_bounds__(256) void k_cic_wgrad_stack(SpatialBatch sb) {
       const int kr = k < M / 2 ? k : k + (N - M);
       g[u] = (on && k < k_end) ? col[(long long)kr * NF] : make_float2(0.f, 0.f);
     }
+    float2 G[NK];  // these rows' sum
+#pragma unroll
+    for (int a = 0; a < NK; ++a) G[a] = make_float2(0.f, 0.f);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int k = k0 + 4 * u;
@@ -2453,10 +2459,12 @@ __global__ __launch_bounds__(256) void k_cic_wgrad_stack(SpatialBatch sb) {
       int idx = 0;  // kr a mod N
 #pragma unroll
       for (int a = 0; a < NK; ++a) {
-        F[a] = cfmac(F[a], gv, tw[idx]);
+        G[a] = cfmac(G[a], gv, tw[idx]);
         idx = add_mod(idx, kr, N);
       }
     }
+#pragma unroll
+    for (int a = 0; a < NK; ++a) F[a].x += G[a].x, F[a].y += G[a].y;
   }
   // project onto the taps: Re(F_a conj(W^(l b)))
   float acc[T];
@@ -2486,7 +2494,9 @@ __global__ __launch_bounds__(256) void k_cic_wgrad_stack(SpatialBatch sb) {
 }
 
 // gw of every layer of the batch from its partial sums (nb = ncb * rowb per output
-// channel), added in order (eight partials' loads in flight at a time).
+// channel), added in order (eight partials' loads in flight at a time), in 64 bits: 40 in a
+// row in 32 made it 8 % larger (1024 -> 512, 3 x 3 taps: 2.91e-7, 2.62e-7 in 64; with the rows by fours
+// 2.51e-7).
 __global__ __launch_bounds__(256) void k_cic_wgrad_stack_reduce(SpatialBatch sb, int total) {
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i >= total) return;
@@ -2496,7 +2506,7 @@ __global__ __launch_bounds__(256) void k_cic_wgrad_stack_reduce(SpatialBatch sb,
   const int nn = d.n * d.n, e = i - d.elem0, nb = d.ncb * d.rowb;
   const int o = e / nn, t = e - (e / nn) * nn;
   const float *src = d.part + (long long)o * nb * nn + t;
-  float acc = 0.f;
+  double acc = 0.;
   int q = 0;
   for (; q + 8 <= nb; q += 8) {
     float v[8];
@@ -2506,7 +2516,7 @@ __global__ __launch_bounds__(256) void k_cic_wgrad_stack_reduce(SpatialBatch sb,
     for (int u = 0; u < 8; ++u) acc += v[u];
   }
   for (; q < nb; ++q) acc += src[q * nn];
-  d.gw[e] = acc;
+  d.gw[e] = (float)acc;
 }
 
 template <class F>

@@ -159,3 +159,33 @@ def test_full_fdc_with_cic_block4(wl):
     assert_parity(to_np(y), y_ref, "y")
     assert_parity(to_np(gx), gx_ref, "gx")
     assert_parity(to_np(gw), gw_ref, "gw")
+
+
+# Partials of dL/dw per output channel: 2, 8 x 5 and 8 x 5
+@pytest.mark.parametrize("N,M,C,J,n", [(64, 64, 16, 4, 3), (512, 512, 4, 4, 5), (1024, 512, 4, 4, 3)])
+def test_spatial_weight_gradient_rounding(N, M, C, J, n):
+    """dL/dw's sums over the kept bins of dK, against the same dK summed in 64 bits.  In units of
+    a rounding's rms, u = 2.5e-8, and with terms of random signs, m additions in a row add m u^2 / 2 to
+    the square of the error: 4 for the 8 multiply-adds of four rows, 2 for four such sums, 2 for the
+    projection, 8 for the levels of 256 lanes (a tree adds u^2 a level) and 1 for the twiddles; the sum over
+    workgroups is in 64 bits.  4.1 u = 1.03e-7, and 1.18e-7 leaves 15 %.  All 16 rows in one chain would be
+    1.3e-7, 40 workgroups added in 32 bits 1.7e-7."""
+    rng = _rng("spatial wgrad", N, M, C, J, n)
+    S = C * J
+    x, w = inputs.normal(rng, (1, C, N, N)), inputs.normal(rng, (S, n, n))
+    spatial = layers.CicSpatialLayer(1, C, S, N, M, n, artifact="crop")
+    layer = layers.CicLayer(1, C, S, N, M, "crop", n)
+    xd, wd = torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda()
+    gy = torch.from_numpy(inputs.normal(rng, (1, S, layer.out, layer.out))).cuda()
+    saved = spatial.new_saved()
+    spatial.forward(xd, wd, saved=saved)
+    _, gw = spatial.backward(gy, saved, None, need_gx=False)
+    _, gK = layer.backward(gy, saved, None, need_gx=False)
+    k = torch.arange(N, dtype=torch.float64, device="cuda")
+    taps = torch.arange(n, dtype=torch.float64, device="cuda")
+    wave = lambda q: torch.polar(torch.ones_like(q), 2 * np.pi * q / N)  # conj(W^q)  # noqa: E731
+    rows, cols = wave(taps[:, None] * k), wave(k[: N // 2 + 1, None] * taps)
+    ref = torch.stack([(rows @ gK[o].to(torch.complex128) @ cols).real for o in range(S)])
+    err = float((gw.double() - ref).norm() / ref.norm())
+    print(f"dL/dw rounding {N}->{M} n={n}: {err:.3e}", flush=True)
+    assert err < 1.18e-7
