@@ -79,12 +79,12 @@ __host__ __device__ constexpr int tap_pad() {
 // columns exchanged: C_a = R_a = sum_b (-1)^b w_ab is real, v_a = W^(k a), K(-k) = conj K(k).
 //
 // What bounds it: matrix and vector issue together.  On gfx950 fp32 MFMA and vector
-// instructions of one SIMD do not overlap, not even from different waves (a probe of both:
+// instructions of one SIMD overlap by under 10 %, also from different waves (a probe of both:
 // 6.3 ms together, 4.6 and 2.3 ms alone), so a step of 64 MFMAs (2048 cycles) and 160 vector
-// instructions (640 cycles) takes at least their sum; measured 3200-3500 cycles, i.e. 80 %.
-// Before (a row per image, bins singly): 16 images of 224^2, 64 -> 64 channels 225 -> 203 us;
-// 4 images of 512^2, 128 -> 128 channels 3.0 -> 1.68 ms; 3 images of 128^2, 48 -> 80 channels,
-// 5 x 5 taps 164 -> 64 us.  BT 8-image tiles share each K: BT = 1 with LB = 4 columns up to 8 images,
+// instructions (640 cycles) takes about their sum; measured 3200-3500 cycles, of which that is 80 %.
+// Before (a row per image, bins singly): 16 images of 224^2, 64 -> 64 channels 223 -> 202 us;
+// 4 images of 512^2, 128 -> 128 channels 2.94 -> 1.13 ms; 3 images of 128^2, 48 -> 80 channels,
+// 5 x 5 taps 159 -> 58 us.  BT 8-image tiles share each K: BT = 1 with LB = 4 columns up to 8 images,
 // BT = 2 with LB = 2 beyond (the same 32 NTL accumulator registers: two waves a SIMD); BT = 1 with LB = 2
 // where the launch has too few workgroups for that to matter.
 // Every load is unconditional: images and channels past the end are clamped to the last
@@ -579,9 +579,11 @@ __global__ __launch_bounds__(256, 3) void k_full_contract4(SpecLayout in, const 
 //   dL/dw[s][c][a][b] = Re sum_bins D conj(u_a(k) v_b(l)),  u_a = W^(k a), v_b = W^(l b).
 // Over a row pair (k, -k), with u_a(-k) = conj u_a(k), P = D(k) + D(-k), Q = D(k) - D(-k):
 //   sum = Re u_a EP_b + Im u_a EQ_b,  EP_b = sum_l Re(P conj v_b), EQ_b = sum_l Im(Q conj v_b),
-// so that a bin costs 2 + 2.5 NK vector instructions (13 of them before at 3 x 3 taps, now 7)
-// and the a-sum is left to the reduction, once per row pair: a workgroup keeps 2 NK sums a
-// (s, c) instead of NK^2.  The Nyquist column l = P/2 runs as one more "row" over k < P/2 with
+// so that a bin costs 1 + 2 NK vector instructions, 7 at 3 x 3 taps (13 with the n^2 sums), and 3
+// more where D comes from Gauss's products.  These, three matrix products for four, take every
+// batch of more than 4 images up to 3 x 3 taps, also an odd number of 4-image steps: 8 images a
+// stage, absent ones zero.  The a-sum is left to the reduction, once per row pair: a workgroup
+// keeps 2 NK sums a (s, c) instead of NK^2.  The Nyquist column l = P/2 runs as one more "row" over k < P/2 with
 // rows k and k + P/2 as its pair: u_a(k + P/2) = (-1)^a u_a(k),
 //   dL/dw += (-1)^b EP_a,  EP_a = sum_k Re((D(k) + (-1)^a D(k + P/2)) conj u_a).
 //
@@ -590,12 +592,13 @@ __global__ __launch_bounds__(256, 3) void k_full_contract4(SpecLayout in, const 
 // columns of both rows for IMG images: 32 G and 32 X planes, LB * 8 bytes each, loaded by LB/2
 // neighbouring lanes and staged in LDS; the loads of stage t + 2 are in flight and stage t + 1
 // is written while stage t is multiplied.  IMG = 8, LB = 8 (64-byte pieces); up to 4 images
-// IMG = 4, LB = 16 (whole 128-byte lines).  What bounds it: matrix plus vector issue (they do
-// not overlap), and reading the spectra from L2, S/32 + C/32 times: with 32-byte pieces (one
+// IMG = 4, LB = 16 (whole 128-byte lines).  What bounds it: matrix plus vector issue (they hardly
+// overlap), and reading the spectra from L2, S/32 + C/32 times: with 32-byte pieces (one
 // run of 4 columns) every piece was a request of its own, 21 TB/s of lines at 256 channels.
-// Measured, pass and reduction, before and after: 16 images of 224^2, 64 x 64 channels 294 ->
-// 205 us, 256 x 256 2.66 -> 2.37 ms; 4 images of 512^2, 128 x 128 1.50 -> 1.13 ms; 3 images of
-// 128^2, 80 x 48, 5 x 5 taps 225 -> 92 us (the NK^2 sums had spilled).
+// Measured, pass and reduction, before and after, 3 x 3 taps: 16 images (Gauss's products) of
+// 224^2, 64 x 64 channels 300 -> 180 us, 256 x 256 2.64 -> 2.35 ms; 4 images (four products) of 512^2,
+// 128 x 128 1.53 -> 1.12 ms; 3 images of 128^2, 80 x 48, 5 x 5 taps 219 -> 66 us (the NK^2 sums had
+// spilled).
 // ---------------------------------------------------------------------------
 template <int IMG>
 struct GwStage {
@@ -1075,8 +1078,9 @@ hipError_t launch_full_gw(int nk, SpecLayout G, SpecLayout X, const float2 *tw, 
     constexpr int NK = decltype(nc)::value;
     auto go = [&](auto ic) {
       constexpr int IMG = decltype(ic)::value;
-      // Gauss's three products pay from two 4-image steps on; with more taps the third
-      // accumulator would spill
+      // Gauss's three products pay in stages of two 4-image steps; with more taps the third
+      // accumulator would spill.  Their error (9, 10, 12 or 18 images, 1 x 1 to 3 x 3 taps) is 0.86 to
+      // 0.97 of four products' with the row pairs added in 32 bits
       constexpr bool kGauss = IMG == 8 && NK <= 3;
       constexpr size_t lds = (size_t)2 * GwStage<IMG>::BUF * sizeof(float2);
       static_assert(lds <= 160 * 1024 && lds >= (size_t)3 * 256 * 8 * NK * sizeof(float), "dL/dw: LDS");

@@ -510,9 +510,10 @@ static int small_jl(int n, int m, long long planes, int J) {
 }
 
 // Where the one-launch forward is the faster one: everywhere (16 planes 11 -> 6 us, 3000 planes
-// of 64 -> 32 63 -> 44; 64 -> 16 with 8 channels 1.04 to 1.07 at 528 and 1040 planes) but for 128 -> 64 and 128 -> 32 with a last round of workgroups that is
-// nearly empty, against separate launches that share the pooled columns between an even number
-// of channels (one launch over separate ones, 16 images a call):
+// of 64 -> 32 63 -> 44; 64 -> 16 with 8 channels 1.04 to 1.07 at 528 and 1040 planes) but for
+// 128 -> 64 and 128 -> 32 with a last round of workgroups that is nearly empty, against separate
+// launches that share the pooled columns between an even number of channels (one launch over
+// separate ones, 16 images a call):
 //   128 -> 64, 256 workgroups a round: 320 planes J = 4, 6, 8, 12: 1.02 to 1.08; 576 planes J = 2,
 //     4, 6, 8: 1.02 to 1.08, but J = 3, 5, 12: 0.95, 0.96, 0.83; 1040 planes J = 1, 2: 1.04, 1.10,
 //     J = 3 to 8: 0.99 to 0.73; full rounds 0.6 to 0.9
@@ -582,10 +583,11 @@ static SmallPlan small_plan(int n, int m, int B, int C, int J) {
 //   128 -> 32: at 2 images 64 to 704 channels of J = 3, 6, 8, 12 1.03 to 1.19 (two ranges of
 //     partial sums against sums written once); at 16 J = 3 1.06 from 2048 planes, J = 12, 16 1.05 to 1.09
 //     at 576 to 704; J = 5 1.03 to 1.26 but for 16 images and 64 to 512 planes, 0.77 to 0.97
-//   64 -> 64: J = 1, 2 0.3 to 1.0 (J = 2, 16 images of 3072 planes 1.05, but
-//     4096 cropped ones, forward and backward, 306 us against 314); J = 3 0.3 to 1.03 up to 511 planes; J = 4 0.55 to 0.97 from 32 to 511 planes, up to 1.17 elsewhere; J >= 5 up to 1.5
-//   128 -> 64: J = 1 0.4 to 0.9; J = 2 0.43 to 1.0 where the rounds of 256 workgroups are full, 1.03 at 320
-//     planes, 1.05 to 1.24 from 576; J >= 3 up to 2.1
+//   64 -> 64: J = 1, 2 0.3 to 1.0 (J = 2, 16 images of 3072 planes 1.05, but 4096 cropped ones,
+//     forward and backward, 306 us against 314); J = 3 0.3 to 1.03 up to 511 planes; J = 4 0.55 to
+//     0.97 from 32 to 511 planes, up to 1.17 elsewhere; J >= 5 up to 1.5
+//   128 -> 64: J = 1 0.4 to 0.9; J = 2 0.43 to 1.0 where the rounds of 256 workgroups are full, 1.03
+//     at 320 planes, 1.05 to 1.24 from 576; J >= 3 up to 2.1
 bool small_bwd_supported(int n, int m, int B, int C, int S) {
   if (!small_layer_supported(n, m)) return false;
   const int J = S / C;
