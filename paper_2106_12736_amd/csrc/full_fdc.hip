@@ -81,7 +81,9 @@ __host__ __device__ constexpr int tap_pad() {
 // What bounds it: matrix and vector issue together.  On gfx950 fp32 MFMA and vector
 // instructions of one SIMD overlap by under 10 %, also from different waves (a probe of both:
 // 6.3 ms together, 4.6 and 2.3 ms alone), so a step of 64 MFMAs (2048 cycles) and 160 vector
-// instructions (640 cycles) takes about their sum; measured 3200-3500 cycles, of which that is 80 %.
+// instructions (640 cycles) takes about their sum.  Matrix plus vector issue is 85 % of the cycles for
+// 16 images of 512^2, 256 -> 256 channels, and 57 % for 224^2, 64 -> 64, whose 1597 workgroups are 3.1
+// rounds of the resident ones with 16 steps each.
 // Before (a row per image, bins singly): 16 images of 224^2, 64 -> 64 channels 223 -> 202 us;
 // 4 images of 512^2, 128 -> 128 channels 2.94 -> 1.13 ms; 3 images of 128^2, 48 -> 80 channels,
 // 5 x 5 taps 159 -> 58 us.  BT 8-image tiles share each K: BT = 1 with LB = 4 columns up to 8 images,
@@ -593,7 +595,8 @@ __global__ __launch_bounds__(256, 3) void k_full_contract4(SpecLayout in, const 
 // neighbouring lanes and staged in LDS; the loads of stage t + 2 are in flight and stage t + 1
 // is written while stage t is multiplied.  IMG = 8, LB = 8 (64-byte pieces); up to 4 images
 // IMG = 4, LB = 16 (whole 128-byte lines).  What bounds it: matrix plus vector issue (they hardly
-// overlap), and reading the spectra from L2, S/32 + C/32 times: with 32-byte pieces (one
+// overlap; 79 % of the cycles for 16 images of 512^2, 256 x 256 channels, 61 % for 224^2, 64 x 64), and
+// reading the spectra from L2, S/32 + C/32 times: with 32-byte pieces (one
 // run of 4 columns) every piece was a request of its own, 21 TB/s of lines at 256 channels.
 // Measured, pass and reduction, before and after, 3 x 3 taps: 16 images (Gauss's products) of
 // 224^2, 64 x 64 channels 300 -> 180 us, 256 x 256 2.64 -> 2.35 ms; 4 images (four products) of 512^2,

@@ -18,8 +18,9 @@ _ARTIFACTS = {"none": ARTIFACT_NONE, "crop": ARTIFACT_CROP, "roll": ARTIFACT_ROL
 
 # The calls of small layers and networks are bound by this file's own work between launches:
 # handles are passed as integers, the current stream is read without building a Stream
-# object, and a tensor that passes its check costs one comparison chain (a forward and
-# backward of 2 images through a 64 -> 32 layer: 27 -> 23 us, of which the GPU takes 18).
+# object (torch's own accessor without one; not a documented function), and a tensor that
+# passes its check costs one comparison chain (a forward and backward of 2 images through a
+# 64 -> 32 layer: 27 -> 22 us, of which the GPU takes 18).
 def _stream():
     return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
